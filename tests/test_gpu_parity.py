@@ -238,6 +238,32 @@ def test_single_kernel_hidden_units_that_are_not_numbers(torch, B_, bits):
     assert np.isfinite(out[[0, 1, 2, 4]]).all() and not np.isfinite(out[3]).any()
 
 
+@pytest.mark.parametrize("path,b", [(None, 5), (None, 40), (1, 5), (2, 5), (3, 5), (4, 5)],
+                         ids=["single", "single-gather", "generic", "stream", "stage", "matrix"])
+def test_activation_over_its_whole_range(torch, B_, path, b):
+    """silu(g) u for gate sums down to -88.5, where 1 + exp(-g) leaves the range whose reciprocal is a normal number:
+    every kernel divides.  Column 0 of W_gate and W_up holds the sums themselves and W_down copies
+    hidden unit c to output c.  Tolerance: 2^-9 for the hidden unit's rounding to bf16, and 2^-9 above the 1e-5 that
+    the fast exponential of 88 can be off."""
+    d, N, I = 2048, 4, 768
+    g = -0.5 * torch.arange(I, device="cuda").remainder(178).float()  # 0 ... -88.5, exact in bf16
+    x = torch.zeros((b, d), dtype=torch.bfloat16, device="cuda")
+    x[:, 0] = 1.0
+    w_router = torch.zeros((N, d), dtype=torch.bfloat16, device="cuda")
+    w_gate = torch.zeros((N, I, d), dtype=torch.bfloat16, device="cuda")
+    w_gate[:, :, 0] = g.bfloat16()
+    w_up = torch.zeros_like(w_gate)
+    w_up[:, :, 0] = 1.0
+    w_down = torch.zeros((N, d, I), dtype=torch.bfloat16, device="cuda")
+    w_down[:, torch.arange(I), torch.arange(I)] = 1.0
+    ws = B_.new_workspace(b, d, N, I, 1)
+    out = B_.moe_decode(x, w_router, w_gate, w_up, w_down, 1, 1, ws, kernel_path=path)
+    torch.cuda.synchronize()
+    ref = torch.zeros(d, dtype=torch.float64, device="cuda")
+    ref[:I] = g.double() / (1 + torch.exp(-g.double()))
+    assert ((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs()).all()
+
+
 def test_generic_kernel_path(torch, B_, oracle):
     """The generic expert kernels (used when the staged token vectors do not fit in LDS) on shapes the
     automatic choice would give to the streaming kernels."""
