@@ -1001,6 +1001,61 @@ def test_deterministic_combine_is_bit_reproducible(torch, B_, oracle):
     assert (out[[2, 9]] == 0).all() and np.abs(out[0]).max() > 0
 
 
+@pytest.mark.parametrize("d,N,B", [(128, 8, 80), (256, 8, 80), (1024, 20, 40)], ids=lambda v: str(v))
+def test_deterministic_bits_do_not_depend_on_the_result_buffer(torch, B_, d, N, B):
+    """A workgroup with few results collects them in LDS, one with many writes them as they come: both add in one
+    order.  With every expert selected (k0 = k = N) a token's row depends on that token alone, so its bits are the
+    same alone (collected) and in a batch whose workgroups have more than the 8192 sums that are collected (8 experts
+    x 2048 hidden units / 256 workgroups = 64 rows x 80 pairs x 2 sums; 160 rows x about 30 pairs staged at once
+    x 2).  Rows of 8, 16 and 32 lanes, fp32 hidden vectors."""
+    I = 2048
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    x = torch.empty((B, d), device="cuda").normal_(generator=gen)
+    w = [torch.empty(s, device="cuda").normal_(0.0, std, generator=gen)
+         for s, std in (((N, d), d ** -0.5), ((N, I, d), 0.02), ((N, I, d), 0.02), ((N, d, I), 0.02))]
+
+    def layer(rows):
+        ws = B_.new_workspace(rows.shape[0], d, N, I, N, deterministic=True)
+        return B_.moe_decode(rows.contiguous(), *w, N, N, ws, deterministic=True, kernel_path=3)
+
+    whole = layer(x)
+    for t in range(0, B, 16):
+        assert torch.equal(layer(x[t:t + 1])[0], whole[t]), "token %d" % t
+
+
+@pytest.mark.parametrize("B,crowded", [(32, (3, 77)), (128, ())], ids=["B32-crowded", "B128"])
+def test_deterministic_bits_of_the_single_kernel(torch, B_, B, crowded):
+    """The single-kernel layers with workgroups on both sides of the limit up to which results are collected in LDS
+    (B=32: two experts that every token selects are above it; B=128: experts with 11 pairs and more).  The same
+    bits on every call, also while the shares of the workgroups still move with their measured speeds, and for
+    every token the bits it has alone (k0 = k, so its weights do not depend on the batch)."""
+    L, dev = big_layer(B_, "qwen3_30b", 2000)
+    k = 8
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B)
+    x = torch.empty((B, L.d), device="cuda").normal_(generator=gen).bfloat16()
+    bias = torch.zeros(L.N, device="cuda")
+    bias[list(crowded)] = 20.0
+    w = [dev[f] for f in ("w_router", "w_gate", "w_up", "w_down")]
+
+    def layer(rows, ws):
+        return B_.moe_decode(rows.contiguous(), *w, k, k, ws, router_bias=bias, deterministic=True, taps=True)
+
+    ws = B_.new_workspace(B, L.d, L.N, L.I, k, deterministic=True)
+    first, tap = layer(x, ws)
+    first = first.clone()
+    assert all(int((tap["expert_idx"] == e).sum()) == B for e in crowded)
+    for it in range(60):
+        assert torch.equal(layer(x, ws)[0], first), "call %d differs" % it
+    ws1 = B_.new_workspace(1, L.d, L.N, L.I, k, deterministic=True)
+    for t in range(B):
+        out, tap1 = layer(x[t:t + 1], ws1)
+        assert torch.equal(tap1["gate_w"][0], tap["gate_w"][t])
+        assert torch.equal(out[0], first[t]), "token %d" % t
+    B_.workspace_check(ws)
+
+
 def test_cooperative_launch_option(torch, B_, oracle):
     """oea_decode_ex.cooperative: the single kernel through a cooperative launch (co-residency is then
     the runtime's guarantee); same results."""
