@@ -82,7 +82,10 @@ int oea_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
  * k0 == k is the unmodified top-k router.
  *
  *   router_logits [B,N] fp32   router pre-activations; ranking is by descending logit, equal
- *                              logits by ascending expert id (-0.0 == +0.0)
+ *                              logits by ascending expert id (-0.0 == +0.0).  A NaN ranks above
+ *                              plus infinity, with its sign bit set below minus infinity (with all bits
+ *                              set it is never selected); the weights of a token that selects one, or
+ *                              an infinity as its best, are NaN
  *   expert_idx    [B,k] int32  S_i in rank order, -1 in unused slots
  *   gate_w        [B,k] fp32   weights, 0 in unused slots, each row sums to 1
  *   n_sel         [B]   int32  |S_i| = min(k, T)

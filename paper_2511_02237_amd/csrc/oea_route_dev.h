@@ -41,7 +41,7 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
 }
 
 // Ranking key of a logit: its order-preserving bit pattern; larger = better rank.  0 marks "not a
-// candidate" (only one negative-NaN pattern maps to 0, and routing of NaN logits is unspecified).
+// candidate" (only the NaN with all bits set maps to 0: it is never selected).
 // Equal keys are separated by expert id when the winner is looked up (lowest id first).
 __device__ __forceinline__ uint32_t make_key(float logit) { return orderable_bits(logit); }
 

@@ -15,10 +15,14 @@
 //   Phase 2 in closed form   everything but the union's other members masked, list of the k - k0 best -> mask
 //   rank order               the experts of each mask, ascending, with their logits fetched again, are
 //                            placed by counting who precedes whom (equal logits: lower id)
+// A median drops logits that are not numbers.  A wavefront that meets one among its candidates ranks all its
+// tokens again by the integer keys of the other routing kernels, so that results do not depend on which kernel
+// a launch takes.
 // 65 535 positions of B = 16, N = 128, k0 = 3: 160 us (4.0 TB/s) instead of 243 us.  A wavefront issues 2 990
 // vector instructions for its four positions (13 950 before); computing alone (logits in the
 // cache) takes 115 us, loading alone 125 us, and two wavefronts per SIMD overlap the two only in part.
 #include "oea_internal.h"
+#include "oea_route_dev.h"
 
 #include <math.h>
 
@@ -48,7 +52,8 @@ __device__ __forceinline__ void lane_best(const float (&v)[NE], float (&best)[C]
 
 // bit e of the words: v[e] >= limit.  The sign of the difference decides, except at infinite limits (two
 // equal infinities differ by a NaN of either sign): everything reaches minus infinity, which is
-// also the limit of a list with free places, and plus infinity is compared with.
+// also the limit of a list with free places, and plus infinity is compared with (what is not a number counts
+// as reaching it).
 template <int NE>
 __device__ __forceinline__ void lane_at_least(const float (&v)[NE], float limit, uint32_t (&m)[NE / 32]) {
 #pragma unroll
@@ -64,7 +69,7 @@ __device__ __forceinline__ void lane_at_least(const float (&v)[NE], float limit,
     for (int w = 0; w < NE / 32; ++w) {
       uint32_t top = 0;
 #pragma unroll
-      for (int b = 31; b >= 0; --b) top = (top << 1) | (v[32 * w + b] == INFINITY ? 1u : 0u);
+      for (int b = 31; b >= 0; --b) top = (top << 1) | (v[32 * w + b] < INFINITY ? 0u : 1u);
       m[w] = limit == INFINITY ? top : m[w];
     }
   }
@@ -96,6 +101,18 @@ __device__ __forceinline__ void lane_cut_ties(const float (&v)[NE], float limit,
       --extra;
     }
   }
+}
+
+// Whether one of the logits is not a number (by the bits: a comparison each would fill the scalar registers).
+template <int NE>
+__device__ __forceinline__ bool lane_any_nan(const float (&v)[NE]) {
+  uint32_t most = 0;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const uint32_t u = __float_as_uint(v[e]) & 0x7fffffffu;
+    most = u > most ? u : most;
+  }
+  return most > 0x7f800000u;
 }
 
 // value at a wave-uniform place of a list (by masks: a chain of selects is taken for an indexed load
@@ -146,6 +163,52 @@ __device__ __forceinline__ void lane_places(const int (&v)[K], int (&place)[K]) 
       place[i] += later_first;
       place[j] -= later_first;
     }
+}
+
+// The routing of a lane's token by the integer keys of the other kernels (make_key), straight from memory: its
+// experts in rank order to ids with their keys, the position's union to U; returns how many experts it has.  `uni`
+// is cleared.  Called by the whole wavefront.  Some k N dependent loads per token: only where a logit is
+// not a number (a launch of NaNs alone is still served, slowly).
+template <int NW>
+__device__ __forceinline__ int lane_rank_by_key(const float* __restrict__ row, bool live, int N, int k, int k0,
+                                                uint32_t* uni, uint32_t (&U)[NW], int* ids, uint32_t* keys) {
+  unsigned long long taken[2] = {0, 0}, cand[2] = {~0ull, ~0ull};
+  int n = 0;
+  auto pick = [&]() __attribute__((always_inline)) {  // the best candidate that is not taken; false if there is none
+    uint32_t top = 0;
+    int id = 0;
+    for (int e = 0; e < N; ++e) {
+      const unsigned long long open = e < 64 ? cand[0] & ~taken[0] : cand[1] & ~taken[1];
+      const uint32_t key = (open >> (e & 63)) & 1 ? make_key(row[e]) : 0;
+      if (key > top) {
+        top = key;
+        id = e;
+      }
+    }
+    if (top == 0) return false;
+    taken[0] |= id < 64 ? 1ull << id : 0;
+    taken[1] |= id < 64 ? 0 : 1ull << (id - 64);
+    ids[n] = id;
+    keys[n] = top;
+    ++n;
+    return true;
+  };
+  if (live) {
+    while (n < k0 && pick()) {
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) atomicOr(&uni[w], uint32_t(taken[w / 2] >> (32 * (w & 1))));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) U[w] = uni[w];
+  cand[0] = U[0] | (unsigned long long)U[1] << 32;
+  cand[1] = NW > 2 ? U[NW > 2 ? 2 : 0] | (unsigned long long)U[NW > 3 ? 3 : 0] << 32 : 0;
+  if (live) {
+    while (n < k && pick()) {
+    }
+  }
+  return n;
 }
 
 // NE: experts rounded up to 64 or 128.  K: most experts per token.  C1: list places of Phase 1.
@@ -221,7 +284,10 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
   }
 
   // ---- Phase 1: the k0 best of every token, united over the position
-  float best[EXACT ? K : K];  // the chosen logits in rank order
+  float best[K];  // the chosen logits in rank order
+  // A selected NaN shows in one of three ways: its sign bit clear, it counts as above the limit and makes the mask
+  // too full; set, it is only reached by a limit of minus infinity, which makes the mask too full as well ...
+  bool odd = false;
   uint32_t m1[NW], m2[NW];
   {
     float b1[C1];
@@ -230,7 +296,10 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
     lane_at_least<NE>(v, limit, m1);
 #pragma unroll
     for (int w = 0; w < NW; ++w) m1[w] &= exists[w];
-    if (__any(lane_count(m1) > k0)) lane_cut_ties<NE>(v, limit, k0, m1);
+    if (__any(lane_count(m1) > k0)) {
+      odd = live && lane_any_nan<NE>(v);
+      lane_cut_ties<NE>(v, limit, k0, m1);
+    }
     if (live) {
 #pragma unroll
       for (int w = 0; w < NW; ++w) atomicOr(&s_union[lpos][w], m1[w]);
@@ -251,7 +320,7 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
   }
 
   // ---- Phase 2: the best members of the union beyond the token's own k0, up to k in all
-  const int n = live ? (T < k ? T : k) : 0;
+  int n = live ? (T < k ? T : k) : 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) m2[w] = EXACT ? U[w] & ~m1[w] : U[w];
   if constexpr (C2 > 0) {
@@ -270,7 +339,10 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
       lane_at_least<NE>(v, limit, at);
 #pragma unroll
       for (int w = 0; w < NW; ++w) m2[w] &= at[w];
-      if (__any(live && lane_count(m2) > n - taken)) lane_cut_ties<NE>(v, limit, n - taken, m2);
+      if (__any(live && lane_count(m2) > n - taken)) {
+        odd |= live && lane_any_nan<NE>(v);
+        lane_cut_ties<NE>(v, limit, n - taken, m2);
+      }
 #pragma unroll
       for (int j = 0; j < C2; ++j) best[taken + j] = b2[j];
     } else {
@@ -282,7 +354,7 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
   // ---- the chosen experts, each group ascending, with their logits (fetched again: registers have no
   // index), then in rank order through LDS (the places are a permutation of 0 .. K-1)
   constexpr int kPitch = K + 1;
-  static_assert(kPitch <= kLanePitch, "fits the staging area");
+  static_assert(2 * kPitch <= kLanePitch, "ids and keys fit the staging area");
   int* const s_ids = reinterpret_cast<int*>(s_stage) + lane * kPitch;
   {
     int id[K], place[K];
@@ -294,6 +366,8 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
 #pragma unroll
     for (int i = 0; i < K; ++i) lv[i] = *reinterpret_cast<const float*>(base + (row_at + uint32_t(id[i]) * 4u));
 #pragma unroll
+    for (int i = 0; i < K; ++i) odd |= i < n && lv[i] != lv[i];  // ... or there was no choice
+#pragma unroll
     for (int i = 0; i < K; ++i) key[i] = i < n ? lane_key(lv[i]) : int(0x80000000u);  // unused places stay behind
     if constexpr (EXACT) lane_places<0, C1>(key, place);
     if constexpr (C2 > 0) lane_places<EXACT ? C1 : 0, C2>(key, place);
@@ -301,6 +375,24 @@ void route_lanes_kernel(const float* __restrict__ logits, const uint8_t* __restr
     for (int i = 0; i < K; ++i) s_ids[place[i]] = i < n ? id[i] : -1;
   }
   __syncthreads();
+  if (__any(odd)) {  // rare
+    uint32_t* const s_keys = reinterpret_cast<uint32_t*>(s_stage) + (kLaneThreads + lane) * kPitch;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s_union[lane][w] = 0;
+    __syncthreads();
+    n = lane_rank_by_key<NW>(logits + (row0 + mine) * N, live, N, k, k0, s_union[lpos], U, s_ids, s_keys);
+    T = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      before[w] = T;
+      T += __popc(U[w]);
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      if (j >= n) s_ids[j] = -1;
+      best[j] = j < n ? from_orderable(s_keys[j]) : -INFINITY;
+    }
+  }
 
   // ---- weights: softmax over the chosen logits (the sum in the order in which the row-per-token
   // kernels take it)

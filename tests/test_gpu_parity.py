@@ -699,6 +699,47 @@ def test_route_batched_lane_per_token(torch, B_, oracle, case):
             assert np.abs(res["gate_w"][l] - ref["gate_w"]).max() <= 1e-6, l
 
 
+NAN_CASES = [  # (L, B, N, k, k0, share of NaN logits in every second position, their bit patterns)
+    (2560, 16, 128, 8, 3, 0.2, (0x7FC00000,)), (2564, 16, 128, 8, 8, 0.01, (0x7FC00000, 0xFFC00000)),
+    (2560, 16, 128, 7, 1, 0.9, (0x7FC00000, 0xFFC00000, 0x7F800001, 0xFF800001, 0x7FFFFFFF, 0xFFFFFFFE)),
+    (2600, 15, 60, 8, 4, 0.95, (0xFFC00000,)), (3840, 16, 96, 12, 5, 0.5, (0x7FC00000, 0xFFC12345)),
+    (6144, 2, 4, 4, 4, 0.3, (0x7FC00000, 0xFFC00000)), (10240, 1, 64, 8, 2, 0.5, (0x7FC00000, 0xFFC00000)),
+    (768, 64, 64, 16, 16, 0.3, (0x7FD00000, 0xFFC00000))]
+
+
+@pytest.mark.parametrize("case", NAN_CASES, ids=lambda c: "L%d-B%d-N%d-k%d-k0%d-%.2f" % c[:6])
+def test_route_batched_logits_that_are_not_numbers(torch, B_, case):
+    """Logits that are not numbers give the same routing in a launch of many positions (a lane per token) as in
+    launches of few (a row of lanes per token): ids distinct, at most k0 per token in the union, neighbours and other
+    positions untouched, and no finite weights for a token that has selected a NaN."""
+    L, B, N, k, k0, share, patterns = case
+    rng = np.random.default_rng(L + N + k)
+    lg = rng.standard_normal((L, B, N), dtype=np.float32)
+    lg[rng.random((L, B, N)) < 0.1] = -np.inf
+    lg[1::7] = np.round(lg[1::7])  # ties
+    lg[5::8, :, :k0] = np.inf      # as many as a token keeps
+    bad = rng.random((L, B, N)) < share
+    bad[::2] = False
+    bad[1::8, ::2] = False  # tokens without a NaN beside tokens with one
+    bad[3::8, 0] = True     # a token of NaNs alone
+    bits = lg.view(np.uint32)
+    bits[bad] = rng.choice(np.array(patterns, np.uint32), int(bad.sum()))
+    mask = (rng.random((L, B)) > 0.2).astype(np.uint8)
+    dl, dm = torch.from_numpy(lg).cuda(), torch.from_numpy(mask).cuda()
+    got = {n: v.cpu().numpy() for n, v in B_.oea_route_batched(dl, k, k0, token_mask=dm).items()}
+    few = 200  # below every size at which a lane takes a token
+    parts = [B_.oea_route_batched(dl[l:l + few], k, k0, token_mask=dm[l:l + few]) for l in range(0, L, few)]
+    ref = {n: np.concatenate([p[n].cpu().numpy() for p in parts]) for n in got}
+    for name in ("n_active", "active_list", "n_sel", "expert_idx"):
+        differ = np.nonzero((got[name] != ref[name]).reshape(L, -1).any(1))[0]
+        assert differ.size == 0, (name, differ[:5], got[name][differ[0]], ref[name][differ[0]])
+    assert np.array_equal(got["gate_w"], ref["gate_w"], equal_nan=True)
+    chosen = np.take_along_axis(lg, np.maximum(got["expert_idx"], 0), 2)
+    used = got["expert_idx"] >= 0
+    hit = (np.isnan(chosen) & used).any(2)
+    assert hit.any() and np.isnan(got["gate_w"][hit][used[hit]]).all()
+
+
 def test_single_kernel_routing_many_batches(torch, B_, oracle):
     """The routing inside the single-kernel layer (rows of 16 lanes, hand-scheduled selection round,
     bookkeeping on the wavefronts without tokens) over many token batches: B = 1..32, every k0, with
