@@ -26,8 +26,9 @@ typedef struct {
                                    where the shape allows
                                4 = three kernels, expert stages on the matrix cores where the shape
                                    allows (bf16; the automatic choice uses them above B = 128) */
-  uint32_t spin_limit;    /* polls after which a wait inside the single kernel gives up
-                             (0 = the default, about a second); 1 forces every wait to give up */
+  uint32_t spin_limit;    /* polls after which a wait inside the single kernel gives up (0 = the
+                             default, about a second; all of a workgroup's hidden vectors count as
+                             one wait, in which a poll takes eight); 1 forces every wait to give up */
   void **h_kernel_events; /* HOST array of 6 hipEvent_t created by the caller, or NULL: recorded on
                              the stream before/after the router+routing kernel [0],[1], the gate/up
                              kernel [2],[3] and the down kernel [4],[5] (the single kernel: [0] before,

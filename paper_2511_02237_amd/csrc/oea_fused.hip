@@ -20,6 +20,7 @@
 #include "oea_ffn_dev.h"
 #include "oea_timeline.h"
 #include "oea_route_dev.h"
+#include "oea_wait.h"
 
 namespace oea {
 
@@ -702,6 +703,7 @@ __global__ __launch_bounds__(kFfnThreads) void moe_fused_kernel(FusedParams p) {
         // staged by the wavefronts that have no weight tiles in flight, unless that would take them
         // more than two rounds of loads (many pairs): then by everybody
         const int kStagers = n16 <= 2 * kFusedStage * n_defer * 64 ? n_defer * 64 : kFfnThreads;
+        WaitBudget budget{spin_limit >> 3};  // for all steps together (a look is a trip to memory: eight polls)
         if (tid < kStagers)
           for (int base = 0; base < n16; base += kFusedStage * kStagers) {
             u32x4 t4[kFusedStage];
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(kFfnThreads) void moe_fused_kernel(FusedParams p) {
             };
 #pragma unroll
             for (int j = 0; j < kFusedStage; ++j) fetch(j);
-            for (uint32_t spins = 0;; ++spins) {
+            while (true) {
               bool any = false;
 #pragma unroll
               for (int j = 0; j < kFusedStage; ++j) {
@@ -724,7 +726,7 @@ __global__ __launch_bounds__(kFfnThreads) void moe_fused_kernel(FusedParams p) {
                 any |= missing[j];
               }
               if (!__any(any)) break;
-              if (spins > (spin_limit >> 3)) {  // (a round is a trip to memory)
+              if (!budget.again()) {
                 if (lane == 0) atomicExch(ctrl + kCtrlErrWord, 1u);
                 break;
               }
@@ -1374,7 +1376,8 @@ hipError_t try_launch_fused(const void* x, const void* w_router, const void* w_g
   p.cap_vec1 = (int)cap_vec1;
   p.ecap0 = ecap0;
   p.ecap1 = ecap1;
-  p.spin_limit = spin_limit ? spin_limit : 4u << 20;  // polls of >= 100 ns each: gives up after about a second
+  // polls of >= 100 ns each, looks at hidden vectors of about 1 us for eight polls: a wait gives up after about a second
+  p.spin_limit = spin_limit ? spin_limit : 4u << 20;
   if (gather) {
     if (shape30) return launch_fused_gather_one<uint16_t, 32, 8, 16, 6, 2>(p, grid, lds_bytes, cooperative, s);
     return launch_fused_gather_one<uint16_t, 64, 8, 32, 6, 2>(p, grid, lds_bytes, cooperative, s);
