@@ -33,6 +33,10 @@ typedef struct {
                              the stream before/after the router+routing kernel [0],[1], the gate/up
                              kernel [2],[3] and the down kernel [4],[5] (the single kernel: [0] before,
                              [1]..[5] after it) */
+  int32_t *h_kernels;     /* HOST array of 2, or NULL: the kernels that the gate/up stage [0] and the down
+                             stage [1] were given to (a kernel_path only asks: a shape that its kernels
+                             do not take runs on others): 0 = the single kernel, 1 = the kernels of paths
+                             1 and 2, 3 and 4 = those of paths 3 and 4 */
 } oea_test_opts;
 
 /*

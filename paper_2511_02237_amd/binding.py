@@ -40,7 +40,7 @@ class DecodeEx(ctypes.Structure):
 
 class TestOpts(ctypes.Structure):  # oea_test_opts of include/oea_testing.h
     _fields_ = [("kernel_path", ctypes.c_int32), ("spin_limit", ctypes.c_uint32),
-                ("h_kernel_events", ctypes.POINTER(ctypes.c_void_p))]
+                ("h_kernel_events", ctypes.POINTER(ctypes.c_void_p)), ("h_kernels", ctypes.POINTER(ctypes.c_int32))]
 
 
 _lib = None
@@ -253,16 +253,18 @@ def _extras(shape, k, dev, router_bias, token_mask, taps, top_p, max_p, cooperat
     return ex, tap
 
 
-def test_opts(kernel_path=None, spin_limit=None, kernel_events=None):
+def test_opts(kernel_path=None, spin_limit=None, kernel_events=None, kernels=None):
     """oea_test_opts (include/oea_testing.h) or None if nothing is set.  kernel_events: ctypes array of
-    6 hipEvent_t handles."""
-    if kernel_path is None and spin_limit is None and kernel_events is None:
+    6 hipEvent_t handles; kernels: ctypes array of 2 int32 that the call fills in."""
+    if kernel_path is None and spin_limit is None and kernel_events is None and kernels is None:
         return None
     o = TestOpts()
     o.kernel_path = int(kernel_path or 0)
     o.spin_limit = int(spin_limit or 0)
     if kernel_events is not None:
         o.h_kernel_events = ctypes.cast(kernel_events, ctypes.POINTER(ctypes.c_void_p))
+    if kernels is not None:
+        o.h_kernels = ctypes.cast(kernels, ctypes.POINTER(ctypes.c_int32))
     return o
 
 

@@ -235,6 +235,9 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   if (ex && ex->max_p > 0 && ex->max_p < N) ga.max_p = ex->max_p;
   const bool general = ga.p < 1.0 || ga.max_p < N;
 
+  auto report = [&](int stage, int kernels) {
+    if (opts && opts->h_kernels) opts->h_kernels[stage] = kernels;
+  };
   if (!mark(0)) return OEA_ERR_HIP;
   hipError_t e = hipErrorNotSupported;
   if (path == 0)
@@ -245,6 +248,8 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   if (e == hipSuccess) {  // one kernel: the inner event pairs collapse onto its end
     for (int i = 1; i < 6; ++i)
       if (!mark(i)) return OEA_ERR_HIP;
+    report(0, 0);
+    report(1, 0);
   } else if (e != hipErrorNotSupported) {
     return OEA_ERR_HIP;
   } else {
@@ -256,18 +261,29 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
     const bool generic_only = path == 1;
     // matrix cores once an expert serves many tokens: above the single kernel's batch range
     const bool dense = path == 4 || (path == 0 && B > kDenseFromBatch);
+    report(0, 4);
     e = dense ? try_launch_dense_stage(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s)
               : hipErrorNotSupported;
-    if (e == hipErrorNotSupported && stage_kernels)
+    if (e == hipErrorNotSupported && stage_kernels) {
+      report(0, 3);
       e = try_launch_stage_kernels(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s);
-    if (e == hipErrorNotSupported) e = launch_expert_gate_up(x, W_gate, W_up, h, B, d, N, I, k, dt, g, generic_only, s);
+    }
+    if (e == hipErrorNotSupported) {
+      report(0, 1);
+      e = launch_expert_gate_up(x, W_gate, W_up, h, B, d, N, I, k, dt, g, generic_only, s);
+    }
     if (e != hipSuccess || !mark(3) || !mark(4)) return OEA_ERR_HIP;
+    report(1, 4);
     e = dense ? try_launch_dense_stage(1, h, W_down, nullptr, nullptr, y ? y : out, B, d, N, I, k, dt, g, y != nullptr, s)
               : hipErrorNotSupported;
-    if (e == hipErrorNotSupported && stage_kernels)
+    if (e == hipErrorNotSupported && stage_kernels) {
+      report(1, 3);
       e = try_launch_stage_kernels(1, h, W_down, nullptr, nullptr, y ? y : out, B, d, N, I, k, dt, g, y != nullptr, s);
-    if (e == hipErrorNotSupported)
+    }
+    if (e == hipErrorNotSupported) {
+      report(1, 1);
       e = launch_expert_down(h, W_down, y ? y : out, B, d, N, I, k, dt, g, generic_only, y != nullptr, s);
+    }
     if (e != hipSuccess || !mark(5)) return OEA_ERR_HIP;
   }
   if (y && launch_combine(y, ro.grp_pos, ro.n_sel, out, B, d, k, s) != hipSuccess) return OEA_ERR_HIP;

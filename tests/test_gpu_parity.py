@@ -9,6 +9,7 @@ they are expected to agree bit for bit; should a logit ever differ (summation or
 the test still requires (i) |d| within one fp32 ulp and (ii) routing identical to the oracle's
 routing OF THE LOGITS THE GPU USED, and compares the output under that routing.
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -184,25 +185,57 @@ STAGE_SHAPES = [  # (B, d, N, I, k, k0, dtype, deterministic)
     (6, 520, 7, 1016, 4, 3, "f32", False),
     # all of x staged (64 KB), just too much for that, and vectors in several pieces of one expert
     (32, 1024, 40, 64, 4, 2, "bf16", False), (33, 1024, 40, 64, 4, 2, "bf16", False), (90, 2048, 2, 64, 2, 1, "bf16", False),
-    # more experts than one step of the row cut, three experts per workgroup, more pairs than threads
-    (64, 64, 300, 32, 6, 4, "bf16", False), (40, 72, 512, 24, 8, 8, "f32", False), (300, 64, 3, 40, 2, 2, "bf16", True)]
+    # more experts than one step of the row cut, three of them in a workgroup's rows, a share that could reach a fourth
+    # (other kernels then), more pairs than threads
+    (64, 64, 300, 32, 6, 4, "bf16", False), (60, 72, 400, 24, 8, 8, "f32", False), (60, 64, 400, 32, 8, 8, "bf16", True),
+    (40, 72, 512, 24, 8, 8, "f32", False), (300, 64, 3, 40, 2, 2, "bf16", True)]
+
+
+def experts_in_a_share(expert_idx, rows, beta, n_wg):
+    """Most experts that one workgroup's rows belong to when the rows (cost 64 + beta x pairs of their expert) are
+    shared by cost."""
+    cost = 64.0 + beta * np.unique(expert_idx[expert_idx >= 0], return_counts=True)[1]
+    ends = np.concatenate([[0.0], np.cumsum(cost)])
+    cut = ends[-1] * np.arange(n_wg + 1) / n_wg
+    e = np.minimum(np.searchsorted(ends, cut, side="right") - 1, cost.size - 1)
+    first = e * rows + ((cut - ends[e]) / cost[e] * rows).astype(int)
+    last = first[1:] - 1
+    return int((last // rows - first[:-1] // rows + 1)[last >= first[:-1]].max())
+
+
+def expert_kernels(torch, B_, dev, k, k0, ws, path, deterministic):
+    """The kernels that a call's two expert stages run on (oea_test_opts.h_kernels)."""
+    args, _, shape = B_._layer_args(*(dev[f] for f in ("x", "w_router", "w_gate", "w_up", "w_down")), k, k0, None)
+    ex, _ = B_._extras(shape, k, "cuda", None, None, False, None, None, deterministic=deterministic)
+    kernels = (ctypes.c_int32 * 2)(-1, -1)
+    opts = B_.test_opts(kernel_path=path, kernels=kernels)
+    B_._check(B_.lib().moe_decode_test(*args, B_._ptr(ws), ws.numel(), B_._stream(None),
+                                       None if ex is None else ctypes.byref(ex), ctypes.byref(opts)))
+    torch.cuda.synchronize()
+    return list(kernels)
 
 
 @pytest.mark.parametrize("shape", STAGE_SHAPES, ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d-%s%s" % (c[:7] + ("-det" if c[7] else "",)))
 def test_stage_kernel_shapes(torch, B_, oracle, shape):
     """The dot-product stage kernels on the row lengths where their tiles change, with the vectors staged whole, per
-    pair and in pieces; a padding token in every batch."""
+    pair and in pieces; a padding token in every batch.  They take a layer if no workgroup's share of the rows can
+    reach a fourth expert."""
     B, d, N, I, k, k0, dtype, det = shape
     L = W.make_layer("toy", 700 + B, d=d, I=I, N=N, B=B, k=k, dtype=dtype)
     mask = np.ones(B, np.uint8)
     mask[B // 2] = 0
     ws = B_.new_workspace(B, d, N, I, k, deterministic=det)
     dev = {f: B_.to_device(getattr(L, f)) for f in ("x", "w_router", "w_gate", "w_up", "w_down")}
+    n_wg = torch.cuda.get_device_properties(0).multi_processor_count
+    taken = 3 if (64 * N + 12 * B * k) // (n_wg * (64 + 3)) < 2 else 1
+    assert expert_kernels(torch, B_, dev, k, k0, ws, 3, det) == [taken, taken]
     outs = []
     for _ in range(2):
         out, tap = B_.moe_decode(dev["x"], dev["w_router"], dev["w_gate"], dev["w_up"], dev["w_down"], k, k0, ws, taps=True,
                                  token_mask=torch.from_numpy(mask).cuda(), deterministic=det, kernel_path=3)
         torch.cuda.synchronize()
+        if N == 400:
+            assert taken == 3 and experts_in_a_share(tap["expert_idx"].cpu().numpy(), d, 12, n_wg) == 3
         outs.append(out.cpu().numpy())
         check_layer(oracle, L, k0, outs[-1], {n: v.cpu().numpy() for n, v in tap.items()}, str(shape), mask=mask)
     if det:
@@ -257,6 +290,8 @@ def test_activation_over_its_whole_range(torch, B_, path, b):
     w_down = torch.zeros((N, d, I), dtype=torch.bfloat16, device="cuda")
     w_down[:, torch.arange(I), torch.arange(I)] = 1.0
     ws = B_.new_workspace(b, d, N, I, 1)
+    dev = dict(x=x, w_router=w_router, w_gate=w_gate, w_up=w_up, w_down=w_down)
+    assert expert_kernels(torch, B_, dev, 1, 1, ws, path, False) == [{None: 0, 2: 1}.get(path, path)] * 2
     out = B_.moe_decode(x, w_router, w_gate, w_up, w_down, 1, 1, ws, kernel_path=path)
     torch.cuda.synchronize()
     ref = torch.zeros(d, dtype=torch.float64, device="cuda")
@@ -1060,6 +1095,9 @@ def test_deterministic_bits_do_not_depend_on_the_result_buffer(torch, B_, d, N, 
         ws = B_.new_workspace(rows.shape[0], d, N, I, N, deterministic=True)
         return B_.moe_decode(rows.contiguous(), *w, N, N, ws, deterministic=True, kernel_path=3)
 
+    dev = dict(zip(("x", "w_router", "w_gate", "w_up", "w_down"), [x] + w))
+    ws = B_.new_workspace(B, d, N, I, N, deterministic=True)
+    assert expert_kernels(torch, B_, dev, N, N, ws, 3, True) == [3, 3]
     whole = layer(x)
     for t in range(0, B, 16):
         assert torch.equal(layer(x[t:t + 1])[0], whole[t]), "token %d" % t
