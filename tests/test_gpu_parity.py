@@ -1077,13 +1077,14 @@ def test_deterministic_combine_is_bit_reproducible(torch, B_, oracle):
     assert (out[[2, 9]] == 0).all() and np.abs(out[0]).max() > 0
 
 
-@pytest.mark.parametrize("d,N,B", [(128, 8, 80), (256, 8, 80), (1024, 20, 40)], ids=lambda v: str(v))
+@pytest.mark.parametrize("d,N,B", [(128, 8, 80), (256, 8, 80), (256, 16, 80), (1024, 20, 40)], ids=lambda v: str(v))
 def test_deterministic_bits_do_not_depend_on_the_result_buffer(torch, B_, d, N, B):
-    """A workgroup with few results collects them in LDS, one with many writes them as they come: both add in one
-    order.  With every expert selected (k0 = k = N) a token's row depends on that token alone, so its bits are the
-    same alone (collected) and in a batch whose workgroups have more than the 8192 sums that are collected (8 experts
-    x 2048 hidden units / 256 workgroups = 64 rows x 80 pairs x 2 sums; 160 rows x about 30 pairs staged at once
-    x 2).  Rows of 8, 16 and 32 lanes, fp32 hidden vectors."""
+    """A workgroup with few results collects their gate and up sums in LDS, with more the results themselves, and with
+    many it writes them as they come: all three add in one order.  With every expert selected (k0 = k = N) a
+    token's row depends on that token alone, so its bits are the same alone (sums collected) and in a batch whose
+    workgroups have more than 4096 results (8 experts x 2048 hidden units / 256 workgroups = 64 rows x 80 pairs;
+    160 rows x about 30 pairs staged at once) or more than 8192 (128 rows x 80 pairs).  Rows of 8, 16 and 32
+    lanes, fp32 hidden vectors."""
     I = 2048
     gen = torch.Generator(device="cuda")
     gen.manual_seed(d)
@@ -1105,10 +1106,10 @@ def test_deterministic_bits_do_not_depend_on_the_result_buffer(torch, B_, d, N, 
 
 @pytest.mark.parametrize("B,crowded", [(32, (3, 77)), (128, ())], ids=["B32-crowded", "B128"])
 def test_deterministic_bits_of_the_single_kernel(torch, B_, B, crowded):
-    """The single-kernel layers with workgroups on both sides of the limit up to which results are collected in LDS
-    (B=32: two experts that every token selects are above it; B=128: experts with 11 pairs and more).  The same
-    bits on every call, also while the shares of the workgroups still move with their measured speeds, and for
-    every token the bits it has alone (k0 = k, so its weights do not depend on the batch)."""
+    """The single-kernel layers with workgroups on both sides of the limit up to which both sums of a result are
+    collected in LDS (B=32: two experts that every token selects are above it; B=128: experts with 11 pairs and
+    more).  The same bits on every call, also while the shares of the workgroups still move with their measured
+    speeds, and for every token the bits it has alone (k0 = k, so its weights do not depend on the batch)."""
     L, dev = big_layer(B_, "qwen3_30b", 2000)
     k = 8
     gen = torch.Generator(device="cuda")
