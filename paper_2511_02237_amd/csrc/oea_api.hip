@@ -48,14 +48,24 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 // batches above this run their expert stages on the matrix cores (three-kernel path)
 static constexpr int kDenseFromBatch = 128;
 
-// Very small layers keep the streaming kernels with fixed shares: a workgroup has a tile or two per
-// stage, and the stage kernels' share by cost, result buffer and pair lists are about 0.7 us per
-// stage that nothing pays back (B=2, d=1352, N=160, I=56: 27.7 us with the stage kernels, 24.7 us without; B=5,
-// d=680, N=16, I=296 fp32: 25.9 / 24.2 us).  From some forty pairs or 16 MB of weights up they win (B=10,
-// d=1168, N=40, I=48: 27.4 / 31.6 us; B=35, d=104, N=40, I=784: 37.6 / 69.4 us).
-static bool little_to_stream(int B, int d, int N, int I, int k, int k0, int elem_bytes) {
-  const long long T = (long long)B * k0 < N ? (long long)B * k0 : N;  // most experts that can be active
-  return (long long)B * k <= 40 && T * 3 * d * I * elem_bytes < (16ll << 20);
+// Stages with little work per wavefront keep the streaming kernels with fixed shares: the stage kernels' share by
+// cost, result buffer and pair lists cost 1 to 2.5 us, and what they save is the pairs' work that fixed shares
+// spread unevenly.  So the line is drawn at the dot products per wavefront (matrix rows x pairs over 256 x 8), whatever
+// the bytes.  Both kernels measured on 370 random layers of B = 1 to 64 outside the single kernel (stream / stage, us):
+//   gate/up  1.5: 6.6 / 9.0 (B=5, d=408, I=40)      11.5: 8.6 / 10.0 (B=3, d=448, I=720 fp32)
+//            10.7: 11.8 / 10.2 (B=11, d=432, I=136)   23: 13.6 / 9.4 (B=11, d=80, I=656)
+//   down     5.7: 8.5 / 9.7 (B=9, d=152, I=280 fp32)  8.8: 8.8 / 10.7 (B=7, d=448, I=784)
+//            13.3: 10.8 / 9.8 (B=11, d=432, I=136)    42: 12.7 / 10.0 (B=10, d=1168, I=48)
+// Against the better of the two at every stage the line at 13 loses 0.35 us a layer (10 to 16 do as well); 27 of the 370
+// layers are more than 0.3 us behind the streaming kernels.  (Drawn by the layer's pairs and bytes, up to 40
+// pairs and 16 MB for the streaming kernels, it lost 0.8 us, and 85 layers were behind.)
+// Where the streaming kernels do not fit (the alternative are the generic ones), the stage kernels in any case.
+static bool prefer_stage_kernels(int stage, int B, int N, int k, int rows, int L, int elem_bytes) {
+  constexpr int kGrid = 256;  // workgroups, one per compute unit (of a whole chip)
+  int cap_vec = 0;
+  size_t lds = 0;
+  return (stage == 0 ? 2ll : 1ll) * B * k * (rows + 64) >= 13ll * 8 * kGrid ||
+         !stream_kernel_fits(stage, B, N, k, L, elem_bytes, kGrid, &cap_vec, &lds);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -257,14 +267,15 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
                                 N, k, k0, dt, logits, y ? y : out, y ? (size_t)B * k * d : (size_t)B * d,
                                 reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, general ? &ga : nullptr, s);
     if (e != hipSuccess || !mark(1) || !mark(2)) return OEA_ERR_HIP;
-    const bool stage_kernels = path == 3 || (path == 0 && !little_to_stream(B, d, N, I, k, k0, elem_bytes_of(dt)));
+    const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, I, d, elem_bytes_of(dt)));
+    const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, d, I, elem_bytes_of(dt)));
     const bool generic_only = path == 1;
     // matrix cores once an expert serves many tokens: above the single kernel's batch range
     const bool dense = path == 4 || (path == 0 && B > kDenseFromBatch);
     report(0, 4);
     e = dense ? try_launch_dense_stage(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s)
               : hipErrorNotSupported;
-    if (e == hipErrorNotSupported && stage_kernels) {
+    if (e == hipErrorNotSupported && gate_up_stage) {
       report(0, 3);
       e = try_launch_stage_kernels(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s);
     }
@@ -276,7 +287,7 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
     report(1, 4);
     e = dense ? try_launch_dense_stage(1, h, W_down, nullptr, nullptr, y ? y : out, B, d, N, I, k, dt, g, y != nullptr, s)
               : hipErrorNotSupported;
-    if (e == hipErrorNotSupported && stage_kernels) {
+    if (e == hipErrorNotSupported && down_stage) {
       report(1, 3);
       e = try_launch_stage_kernels(1, h, W_down, nullptr, nullptr, y ? y : out, B, d, N, I, k, dt, g, y != nullptr, s);
     }

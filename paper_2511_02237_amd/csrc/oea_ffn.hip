@@ -20,7 +20,6 @@ namespace oea {
 namespace {
 
 constexpr size_t kLdsBudget = 128 * 1024;     // generic kernel: LDS bytes for the staged token vectors
-constexpr size_t kStreamLdsMax = 152 * 1024;  // streaming kernel: most LDS one workgroup may ask for
 
 struct FfnParams {
   const void* wa;    // stage 0: W_gate [N,rows,L]; stage 1: W_down [N,rows,L]
@@ -380,23 +379,14 @@ hipError_t launch_stream_lpr(const FfnParams& p, size_t lds_bytes, hipStream_t s
   return launch_stream_one<WT, STAGE, LPR, 8, RG, false>(p, lds_bytes, s);
 }
 
-// Streaming kernel if a row fits 8 chunks of some lanes-per-row and the staged vectors fit LDS.
-// Returns hipErrorNotSupported when the generic kernel has to be used.
+// Streaming kernel if the stage fits it.  Returns hipErrorNotSupported when the generic kernel has to be used.
 template <typename WT>
 hipError_t try_launch_stream(int stage, FfnParams p, int B, int k, hipStream_t s) {
   constexpr int EPL = 16 / int(sizeof(WT));
-  const int grid = num_cus();
-  const int nseg_max = (p.N + grid - 1) / grid + 1;
-  if (nseg_max > kMaxSeg || p.L > 64 * EPL * 8) return hipErrorNotSupported;
-  long long cap_vec = (long long)nseg_max * B;
-  if (cap_vec > (long long)B * k) cap_vec = (long long)B * k;
-  const size_t list_bytes = 16 + (((size_t)cap_vec * 8 + 15) / 16) * 16;  // dump slot + pair lists
-  const size_t vec_bytes = (size_t)(stage == 0 ? B : cap_vec) * p.L * sizeof(WT);
-  size_t lds_bytes = list_bytes + vec_bytes;
-  if (lds_bytes > kStreamLdsMax) return hipErrorNotSupported;
+  size_t lds_bytes = 0;
+  if (!stream_kernel_fits(stage, B, p.N, k, p.L, sizeof(WT), num_cus(), &p.cap_vec, &lds_bytes)) return hipErrorNotSupported;
   const size_t alone = 84 * 1024;  // more than half of the CU's 160 KB: one workgroup per CU
   if (lds_bytes < alone) lds_bytes = alone;
-  p.cap_vec = (int)cap_vec;
   // fewest lanes per row (most rows per tile) that covers a row in at most 8 chunks
   const int lpr = p.L <= 16 * EPL * 8 ? 16 : (p.L <= 32 * EPL * 8 ? 32 : 64);
   if (stage == 0) {

@@ -118,6 +118,24 @@ hipError_t launch_router_and_route(const void* x, const void* w_router, const fl
                                    RouteOut o, const RouteGeneralArgs* general, hipStream_t s);
 hipError_t launch_route_general(const float* logits, const uint8_t* token_mask, int B, int N, int k0,
                                 const RouteGeneralArgs& ga, int32_t* n_base, RouteOut o, hipStream_t s);
+// most experts a workgroup's rows may belong to
+constexpr int kMaxSeg = 3;
+constexpr size_t kStreamLdsMax = 152 * 1024;  // streaming kernel: most LDS one workgroup may ask for
+
+// The streaming kernel's plan for a stage (0 gate/up, 1 down) with rows of L elements: whether a row fits 8 chunks of
+// some lanes-per-row and the staged vectors (gate/up: x of the batch; down: the pairs of a workgroup's experts) fit LDS.
+inline bool stream_kernel_fits(int stage, int B, int N, int k, int L, size_t elem_bytes, int grid, int* cap_vec,
+                               size_t* lds_bytes) {
+  const int nseg_max = (N + grid - 1) / grid + 1;
+  if (nseg_max > kMaxSeg || (size_t)L * elem_bytes > 64 * 16 * 8) return false;
+  long long cap = (long long)nseg_max * B;
+  if (cap > (long long)B * k) cap = (long long)B * k;
+  *cap_vec = (int)cap;
+  const size_t list_bytes = 16 + (((size_t)cap * 8 + 15) / 16) * 16;  // dump slot + pair lists
+  *lds_bytes = list_bytes + (size_t)(stage == 0 ? B : cap) * L * elem_bytes;
+  return *lds_bytes <= kStreamLdsMax;
+}
+
 // generic_only: skip the streaming kernels with fixed shares (test aid)
 hipError_t launch_expert_gate_up(const void* x, const void* w_gate, const void* w_up, void* h, int B,
                                  int d, int N, int I, int k, oea_dtype dt, Grouping g, bool generic_only,

@@ -242,6 +242,22 @@ def test_stage_kernel_shapes(torch, B_, oracle, shape):
         assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
 
 
+@pytest.mark.parametrize("shape", [
+    (3, 448, 40, 720, 5, 2, "f32", [1, 1]), (11, 80, 64, 656, 3, 3, "bf16", [3, 1]), (10, 1168, 40, 48, 7, 2, "bf16", [1, 3]),
+    (13, 448, 24, 160, 8, 4, "f32", [3, 3]),
+    # little work, but more vectors than the streaming kernels can stage
+    (50, 4096, 8, 16, 1, 1, "bf16", [3, 3])], ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d-%s" % c[:7])
+def test_kernels_chosen_per_stage(torch, B_, oracle, shape):
+    """Each stage of a layer outside the single kernel takes the streaming or the stage kernels by its own size; all
+    four pairs of them give the layer."""
+    B, d, N, I, k, k0, dtype, kernels = shape
+    L = W.make_layer("toy", 1100 + B, d=d, I=I, N=N, B=B, k=k, dtype=dtype)
+    dev = {f: B_.to_device(getattr(L, f)) for f in ("x", "w_router", "w_gate", "w_up", "w_down")}
+    assert expert_kernels(torch, B_, dev, k, k0, B_.new_workspace(B, d, N, I, k), None, False) == kernels
+    out, tap = run_layer_dev(torch, B_, L, dev, k0)
+    check_layer(oracle, L, k0, out, tap, str(shape))
+
+
 @pytest.mark.parametrize("shape", [(129, 8, 3, "bf16"), (144, 32, 16, "bf16"), (145, 264, 17, "f32"), (160, 1032, 130, "bf16"),
                                    (131, 4096, 33, "bf16"), (250, 2056, 64, "f32"), (1024, 40, 512, "bf16")],
                          ids=lambda c: "B%d-d%d-N%d-%s" % c)
