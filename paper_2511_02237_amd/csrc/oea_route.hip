@@ -33,12 +33,12 @@ __global__ __launch_bounds__(NT) void route_kernel(const float* logits, const ui
     // positions the launch is bound by how many are resident to hide each other's LDS round trips)
     RowCarry<4 * NV> c;
     route_union_rows<4 * NV, NT>(logits, token_mask, B, N, k0, o, lds, c);
-    route_fill_rows<4 * NV, NT>(B, N, k, k0, o, lds, c);
+    route_fill_rows<4 * NV, NT, false>(B, N, k, k0, o, lds, c);
   } else if (NV <= 2 && k <= 16 && B <= 4 * (NT / 64)) {
     // few experts: one DPP row of 16 lanes per token, four tokens per wavefront
     RowCarry<4 * NV> c;
     route_union_rows<4 * NV, NT>(logits, token_mask, B, N, k0, o, lds, c);
-    route_fill_rows<4 * NV, NT>(B, N, k, k0, o, lds, c);
+    route_fill_rows<4 * NV, NT, false>(B, N, k, k0, o, lds, c);
   } else if (NV <= 2 && k <= 16 && B <= 16 * (NT / 64)) {
     route_rows_groups<4 * NV, NT, 4>(logits, token_mask, B, N, k, k0, o, lds);  // up to four groups, keys kept
   } else if (NV <= 2 && k <= 16) {
