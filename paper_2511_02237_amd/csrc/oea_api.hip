@@ -59,13 +59,19 @@ static constexpr int kDenseFromBatch = 128;
 // Against the better of the two at every stage the line at 13 loses 0.35 us a layer (10 to 16 do as well); 27 of the 370
 // layers are more than 0.3 us behind the streaming kernels.  (Drawn by the layer's pairs and bytes, up to 40
 // pairs and 16 MB for the streaming kernels, it lost 0.8 us, and 85 layers were behind.)
-// Where the streaming kernels do not fit (the alternative are the generic ones), the stage kernels in any case.
-static bool prefer_stage_kernels(int stage, int B, int N, int k, int rows, int L, int elem_bytes) {
+// Two cases stand outside that line.  A workgroup whose experts' pairs do not fit LDS at once walks them in pieces and
+// streams its rows again for each: not if two experts of average size do not fit with a quarter to spare
+// (gate/up of B=42, d=624, N=16, k=7 fp32: 18 pairs per expert, 30 vectors, 19.7 / 27.7).  And where the streaming
+// kernels do not fit, the alternative being the generic ones, the stage kernels in any case.
+static bool prefer_stage_kernels(int stage, int B, int N, int k, int k0, int rows, int L, int elem_bytes) {
   constexpr int kGrid = 256;  // workgroups, one per compute unit (of a whole chip)
   int cap_vec = 0;
   size_t lds = 0;
-  return (stage == 0 ? 2ll : 1ll) * B * k * (rows + 64) >= 13ll * 8 * kGrid ||
-         !stream_kernel_fits(stage, B, N, k, L, elem_bytes, kGrid, &cap_vec, &lds);
+  if (!stream_kernel_fits(stage, B, N, k, L, elem_bytes, kGrid, &cap_vec, &lds)) return true;
+  const long long pairs = (long long)B * k, T = (long long)B * k0 < N ? (long long)B * k0 : N;  // most active experts
+  if ((stage == 0 ? 2 : 1) * pairs * (rows + 64) < 13ll * 8 * kGrid) return false;
+  const StageLds plan = plan_stage(stage, B, N, k, stage_pitch(L * elem_bytes / 16));
+  return plan.whole || plan.cap_vec >= plan.cap_list || 5 * pairs <= 2 * T * plan.cap_vec;
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -267,8 +273,8 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
                                 N, k, k0, dt, logits, y ? y : out, y ? (size_t)B * k * d : (size_t)B * d,
                                 reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, general ? &ga : nullptr, s);
     if (e != hipSuccess || !mark(1) || !mark(2)) return OEA_ERR_HIP;
-    const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, I, d, elem_bytes_of(dt)));
-    const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, d, I, elem_bytes_of(dt)));
+    const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, k0, I, d, elem_bytes_of(dt)));
+    const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, k0, d, I, elem_bytes_of(dt)));
     const bool generic_only = path == 1;
     // matrix cores once an expert serves many tokens: above the single kernel's batch range
     const bool dense = path == 4 || (path == 0 && B > kDenseFromBatch);

@@ -26,9 +26,7 @@ namespace oea {
 
 namespace {
 
-constexpr size_t kFusedLdsMax = 156 * 1024;
 #define OEA_MAX_FUSED_N 128  // experts the fused kernel handles (completion words in the control area)
-constexpr int kFusedStage = 8;  // staging loads kept in flight per thread
 // Small-batch kernel, down stage: two wavefronts (few active experts) or one request no weight
 // tiles before the hidden vectors are there, and stage them (see fused_stage).
 // Measured at B=16: -1.2 us with two at T=36, but +0.4 us at T=73, where one is neutral.
@@ -1192,19 +1190,14 @@ __global__ __launch_bounds__(kFfnThreads) void expert_stage_kernel(StageParams p
 template <typename WT, int STAGE, int LPR, int NCH, int RG, bool PAD>
 hipError_t launch_stage_one(StageParams p, int grid, hipStream_t s) {
   auto kern = expert_stage_kernel<WT, STAGE, LPR, NCH, RG, PAD>;
-  // LDS plan: lists, then as many vectors as fit beside a result buffer of 1024 floats per wavefront
-  p.cap_list = kMaxSeg * p.B < p.pairs_max ? kMaxSeg * p.B : p.pairs_max;
-  const size_t vec_bytes = (size_t)LPR * NCH * 16;
-  const size_t fixed = 16 + ((2 * (size_t)p.N + 8 + 2 * (size_t)p.cap_list + 3) / 4) * 16;
-  p.ecap = 1024;
-  const size_t res = (size_t)p.ecap * kFfnWaves * sizeof(float);
-  if (fixed + res + vec_bytes > kFusedLdsMax) return hipErrorNotSupported;
-  size_t cap = (kFusedLdsMax - fixed - res) / vec_bytes;
-  p.whole = STAGE == 0 && (size_t)p.B <= cap && p.B * LPR * NCH <= kFusedStage * kFfnThreads;
-  const size_t most = p.whole ? (size_t)p.B : (size_t)p.cap_list;
-  if (cap > most) cap = most;
-  p.cap_vec = (int)cap;
-  size_t lds = fixed + cap * vec_bytes + res;
+  // lists, then as many vectors as fit beside the result buffer
+  const StageLds plan = plan_stage(STAGE, p.B, p.N, p.pairs_max / p.B, LPR * NCH);
+  if (plan.cap_vec == 0) return hipErrorNotSupported;
+  p.cap_list = plan.cap_list;
+  p.cap_vec = plan.cap_vec;
+  p.whole = plan.whole;
+  p.ecap = kStageResultFloats / kFfnWaves;
+  size_t lds = plan.bytes;
   const size_t alone = 84 * 1024;  // more than half of a compute unit's LDS: one workgroup per compute unit
   if (lds < alone) lds = alone;
   static PerDevice attr_set;
@@ -1219,6 +1212,7 @@ hipError_t launch_stage_one(StageParams p, int grid, hipStream_t s) {
 template <typename WT, int STAGE>
 hipError_t launch_stage_shaped(StageParams p, int grid, hipStream_t s) {
   constexpr int EPL = 16 / int(sizeof(WT));
+  // (stage_pitch follows the same list)
   constexpr int RG4 = STAGE == 0 ? 2 : 4, RG8 = STAGE == 0 ? 1 : 2;
   switch (p.L / EPL) {  // rows that a shape covers exactly (bf16: 192, 384, 768, 1024, 1536, 2048, 4096 columns)
     case 24: return launch_stage_one<WT, STAGE, 8, 3, RG4, false>(p, grid, s);

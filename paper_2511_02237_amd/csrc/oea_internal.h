@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <initializer_list>
 
 #include "oea.h"
 #include "oea_testing.h"
@@ -134,6 +135,40 @@ inline bool stream_kernel_fits(int stage, int B, int N, int k, int L, size_t ele
   const size_t list_bytes = 16 + (((size_t)cap * 8 + 15) / 16) * 16;  // dump slot + pair lists
   *lds_bytes = list_bytes + (size_t)(stage == 0 ? B : cap) * L * elem_bytes;
   return *lds_bytes <= kStreamLdsMax;
+}
+
+// The stage kernels' plan for a stage with rows of L elements (`granules` of 16 bytes): their tiles cover some row
+// lengths exactly and pad the others.
+constexpr size_t kFusedLdsMax = 156 * 1024;
+constexpr int kFfnThreads = 512;
+constexpr int kFusedStage = 8;                               // staging loads kept in flight per thread
+constexpr int kStageResultFloats = 1024 * kFfnThreads / 64;  // result buffer: 1024 per wavefront
+inline int stage_pitch(int granules) {  // granules between staged vectors; 0: too long a row
+  for (int exact : {24, 48, 96, 192})
+    if (granules == exact) return exact;
+  for (int p = 32; p <= 512; p *= 2)
+    if (granules <= p) return p;
+  return 0;
+}
+struct StageLds {
+  int cap_list = 0;  // entries of a workgroup's pair lists: every pair of kMaxSeg experts
+  int cap_vec = 0;   // vectors staged at a time; 0: not even one fits
+  bool whole = false;  // gate/up: x of the batch is staged, at most kFusedStage granules per thread
+  size_t bytes = 0;
+};
+inline StageLds plan_stage(int stage, int B, int N, int k, int pitch) {
+  StageLds p;
+  p.cap_list = kMaxSeg * B < B * k ? kMaxSeg * B : B * k;
+  const size_t vec_bytes = (size_t)pitch * 16, res = (size_t)kStageResultFloats * sizeof(float);
+  const size_t fixed = 16 + ((2 * (size_t)N + 8 + 2 * (size_t)p.cap_list + 3) / 4) * 16;
+  if (pitch == 0 || fixed + res + vec_bytes > kFusedLdsMax) return p;
+  size_t cap = (kFusedLdsMax - fixed - res) / vec_bytes;
+  p.whole = stage == 0 && (size_t)B <= cap && B * pitch <= kFusedStage * kFfnThreads;
+  const size_t most = p.whole ? (size_t)B : (size_t)p.cap_list;
+  if (cap > most) cap = most;
+  p.cap_vec = (int)cap;
+  p.bytes = fixed + cap * vec_bytes + res;
+  return p;
 }
 
 // generic_only: skip the streaming kernels with fixed shares (test aid)

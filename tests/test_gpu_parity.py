@@ -245,6 +245,8 @@ def test_stage_kernel_shapes(torch, B_, oracle, shape):
 @pytest.mark.parametrize("shape", [
     (3, 448, 40, 720, 5, 2, "f32", [1, 1]), (11, 80, 64, 656, 3, 3, "bf16", [3, 1]), (10, 1168, 40, 48, 7, 2, "bf16", [1, 3]),
     (13, 448, 24, 160, 8, 4, "f32", [3, 3]),
+    # work enough, but more pairs per expert than the stage kernels stage at once
+    (42, 624, 16, 152, 7, 3, "f32", [1, 3]),
     # little work, but more vectors than the streaming kernels can stage
     (50, 4096, 8, 16, 1, 1, "bf16", [3, 3])], ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d-%s" % c[:7])
 def test_kernels_chosen_per_stage(torch, B_, oracle, shape):
