@@ -158,7 +158,7 @@ def route_throughput(args):
 
 TIMELINE_SLOTS = ["kernel entered", "logits stored, x staged", "grid barrier passed", "candidate keys in registers",
                   "Phase 1 done, union complete", "Phase 2 and gate weights done", "CSR offsets done",
-                  "routing and row cuts done", "gate/up rows streamed, h written", "completion announced",
+                  "routing and row cuts done", "gate/up rows streamed, h written", "completion announced (B > 32)",
                   "first down tiles requested", "hidden vectors of own experts complete", "hidden vectors staged",
                   "down rows streamed, adds issued", "adds drained"]
 

@@ -45,7 +45,10 @@ static int check_route_sizes(int B, int N, int k, int k0) {
   return OEA_OK;
 }
 
-// batches above this run their expert stages on the matrix cores (three-kernel path)
+// Batches above this run their expert stages on the matrix cores (three-kernel path); it is the end of the single
+// kernel's range.  On a fixed batch of 128 tokens the single kernel leads on the 30B shape (213 against 229 us), with
+// batches that change from call to call it leads up to B = 96 (204 / 212; B=128: 236 / 224), on the 235B
+// shape up to B = 64 (615 / 634; B=96: 770 / 742, B=128: 1062 / 782).
 static constexpr int kDenseFromBatch = 128;
 
 // Stages with little work per wavefront keep the streaming kernels with fixed shares: the stage kernels' share by

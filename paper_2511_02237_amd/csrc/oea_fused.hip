@@ -393,8 +393,8 @@ __device__ __forceinline__ void fused_stage(const WT* wa, const WT* wb, WT* h_ou
 
   uint4 wA[NM][RG][NCH], wB[NM][RG][NCH];
   int rA = lo, nA = 0, rB = lo, nB = 0;
-  // The first n_defer wavefronts request nothing before mid: what they load IN mid (polled counters,
-  // staged vectors) then does not queue behind two weight tiles (loads return in issue order).
+  // The first n_defer wavefronts request nothing before mid: what they load IN mid (staged vectors,
+  // polled counters or marks) then does not queue behind two weight tiles (loads return in issue order).
   if (wg_has && !deferred) {  // a wavefront that finds no tile requests a placeholder
     take_tile(rA, nA, wave - n_defer);
     take_tile(rB, nB, nw + wave - n_defer);

@@ -18,7 +18,7 @@
 // A median drops logits that are not numbers.  A wavefront that meets one among its candidates ranks all its
 // tokens again by the integer keys of the other routing kernels, so that results do not depend on which kernel
 // a launch takes.
-// 65 535 positions of B = 16, N = 128, k0 = 3: 160 us (4.0 TB/s) instead of 243 us.  A wavefront issues 2 990
+// 65 535 positions of B = 16, N = 128, k0 = 3: 160 us (4.0 TB/s) instead of 243 us.  A wavefront issues 3 051
 // vector instructions for its four positions (13 950 before); computing alone (logits in the
 // cache) takes 115 us, loading alone 125 us, and two wavefronts per SIMD overlap the two only in part.
 #include "oea_internal.h"
