@@ -289,9 +289,13 @@ __global__ __launch_bounds__(kFfnThreads) void expert_dense_kernel(DenseParams p
   const long long U = (long long)T * upe;
   // Consecutive shares go to workgroups of the same XCD (workgroups are dealt out to the eight in turn), so
   // the units of an expert find its token rows in one L2 instead of fetching them into all eight
-  // (B=1000, d=4096, I=1536: gate/up 567 -> 558 us, down 336 -> 328 us).
+  // (B=1000, d=4096, I=1536: gate/up 567 -> 558 us, down 336 -> 328 us; layers up to 2.4 GB of active weights 0 to 2 %).
+  // Not with more than 3 GB of them and few tokens per expert, where the stream of weights suffers (layer, XCD order /
+  // in turn, us: d=4096, N=128, I=1024 564 / 534 at B=200 and 577 / 557 at B=400, I=1536 813 / 803 at B=200, 818 / 817 at
+  // B=400, 856 / 859 at B=640, 893 / 898 at B=800).
   const int G = int(gridDim.x), per_xcd = G / 8;
-  const int share = G % 8 == 0 ? int(blockIdx.x % 8) * per_xcd + int(blockIdx.x / 8) : int(blockIdx.x);
+  const bool by_xcd = G % 8 == 0 && ((long long)T * p.rows * p.L <= 500000000ll || l_off[T] >= 40 * T);
+  const int share = by_xcd ? int(blockIdx.x % 8) * per_xcd + int(blockIdx.x / 8) : int(blockIdx.x);
   const int u0 = int(U * share / G), u1 = int(U * (share + 1) / G);
   u32x4_t* const lds_a = reinterpret_cast<u32x4_t*>(lds4) + wave * kDenseLdsA;
   u32x4_t* const lds_b = reinterpret_cast<u32x4_t*>(lds4) + kFfnWaves * kDenseLdsA;
