@@ -7,23 +7,23 @@
 // instead: v_mfma_f32_16x16x32_bf16 multiplies 16 weight rows x 32 columns with the same 32
 // entries of 16 token vectors (bf16 products, fp32 accumulation).
 //
-// A workgroup (8 wavefronts) takes units of 128 rows of W_gate AND W_up of one expert (gate/up
-// stage; 16 rows of each per wavefront) or 256 rows of W_down (down stage; 32 per wavefront) and
-// walks the inner dimension in slabs of 64 columns, against up to 128 tokens of the expert at a
-// time (accumulators for 8 groups of 16 tokens x 2 weight tiles stay in registers; an expert with
-// more tokens takes further passes over the same rows).
-//   * Every operand is loaded from memory with whole 128-byte row pieces per 8 lanes (a lane
-//     pattern in the instruction's operand layout, 16 different rows per 16 lanes, costs several
-//     times the cache look-ups and was measured to stream at half the rate), four slabs ahead,
-//     into registers; loads are issued and consumed in one order, so the in-order completion of
-//     the memory counter costs nothing.  The pipeline runs on across units.
-//   * A slab goes through LDS to reach the operand layout (lane l: row l % 16, columns
-//     8 (l / 16) .. + 8 of a step's 32): a wavefront's weight rows through a region of its own, the
-//     token rows (x, or h rows of the expert's pairs, gathered through the pair list; each
-//     wavefront loads an eighth) through a shared one, two buffers each and one workgroup barrier
-//     per slab.  Rows are 144 bytes apart in LDS, so both directions are free of bank conflicts.
-// Results leave the registers directly: silu(gate) * up rounded to the storage type into h, or
-// gate-weighted atomic adds into out (Eq. 1).
+// A workgroup takes an equal share of all active experts' rows, in granules of 16 rows of W_gate AND
+// W_up (gate/up stage) or 32 rows of W_down (down stage), and works through it in jobs of up to eight
+// granules of one expert against up to 128 of its tokens (an expert with more takes further passes over
+// the same rows), walking the inner dimension in slabs of 64 columns.  Its twelve wavefronts have two roles:
+//   * Four load: every operand goes from memory straight into LDS (global_load_lds, 16 bytes per lane, whole
+//     128-byte row pieces per 8 lanes), two to five slabs ahead of their use, across jobs.  Loads are all that their memory counter counts, so waiting for the oldest slab never
+//     waits for anything else.
+//   * Eight multiply, a granule each.  Their results leave the registers directly at the end of a job: silu(gate) * up rounded to the storage type into h, or gate-weighted atomic adds into
+//     out (Eq. 1).  These stores and adds are in no one's way.
+// One workgroup barrier per slab orders the two: the slab has landed, the slab before it is used up.
+//
+// Bound by the weight stream: a loop of these requests alone reaches 7.0 TB/s with two slabs of 32 KB in flight per
+// compute unit (128-byte pieces or whole rows, one barrier per slab or none; 6.2 without the non-temporal hint); the
+// kernel without its results 6.3 to 6.5.  What is left are the results (B=512, d=2048, I=768: gate/up 13 us,
+// down 17 us; B=1000, d=4096, I=1536: 37 and 64 us).  Before, every wavefront loaded into registers, multiplied and wrote
+// its results, and the first slab of a job waited for the results of the one before (gate/up + down, us, before /
+// now: B=512, d=2048, I=768 139 + 83 / 136 + 83; B=1000, d=4096, I=1536 560 + 330 / 549 + 319).
 #include "oea_ffn_dev.h"
 
 namespace oea {
@@ -35,14 +35,15 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kDenseGroups = 8;     // groups of 16 tokens per pass
 constexpr int kDenseTokens = 16 * kDenseGroups;
-constexpr int kDenseBLoads = kDenseTokens / 64;  // token-row pieces a lane loads per slab (8 rows per wavefront and load)
 constexpr int kDenseSlab = 64;      // columns per slab: two matrix-core steps of 32
-constexpr int kDenseLook = 4;       // slabs requested ahead
-constexpr int kDenseRowQuads = 9;   // 16-byte pieces between consecutive rows of a slab in LDS (8 + 1 of padding)
-constexpr int kDenseLdsA = 2 * 2 * 16 * kDenseRowQuads;          // per wavefront: [buffer][tile][row]
-constexpr int kDenseLdsB = 2 * kDenseTokens * kDenseRowQuads;    // [buffer][token]
-constexpr int kDenseMeta = 4096;    // pairs whose token and gate weight a workgroup keeps in LDS
-constexpr size_t kDenseLdsBytes = (size_t)(kFfnWaves * kDenseLdsA + kDenseLdsB) * 16 + (size_t)kDenseMeta * 8;
+constexpr int kMaxRing = 6;         // most slabs in LDS
+constexpr int kMulWaves = 8;        // wavefronts that multiply; a job's most granules
+constexpr int kLoadWaves = 4;       // wavefronts that load: two granules and 32 token rows each
+constexpr int kDenseThreads = 64 * (kMulWaves + kLoadWaves);
+constexpr int kRowBytes = kDenseSlab * 2;                  // of a slab in LDS
+constexpr int kRows32 = 32 * kRowBytes;                    // a granule's rows (16 + 16 in the gate/up stage), or 32 token rows
+constexpr int kRingBytes = 3 * (kMulWaves + kDenseTokens / 32) * kRows32;  // three of the largest slabs
+constexpr size_t kDenseLdsBytes = (size_t)kRingBytes + (size_t)kDenseTokens * 8;
 
 struct DenseParams {
   const uint16_t* wa;   // gate/up stage: W_gate; down stage: W_down   [N, rows, L]
@@ -53,184 +54,213 @@ struct DenseParams {
   Grouping g;
   int rows, L, N, B, pairs_max;
   int per_pair;
+  int divisors;  // bit c: an expert's granules are a multiple of c
 };
 
-// One job of a workgroup: a unit (expert, block of rows) against one pass of at most kDenseTokens pairs.
+// One job of a workgroup: granules of one expert against one pass of at most kDenseTokens pairs.
 struct DenseJob {
-  int u;      // unit number; units are numbered expert-major over the active list
+  int u;      // first granule; granules are numbered expert-major over the active list
+  int n;      // granules, 1..kMulWaves; 0: no further job
   int pass;
   int e;      // expert id
-  int row0;   // first row of the unit inside the expert
+  int row0;   // first row of the job inside the expert
   int pair0;  // first pair of the pass (grouped order)
   int cnt;    // pairs in the pass, 1..kDenseTokens
-  int mbase;  // entry of pair0 in the token / gate-weight copy in LDS
-  bool valid;
 };
 
-// Token and gate weight of the pairs of the workgroup's experts are copied to LDS before the first
-// weight request: a load from memory inside the pipeline would have to wait for every weight load
-// issued before it (the memory counter completes in order).  A workgroup's units span at most
-// ceil(N / workgroups) + 1 experts of at most B pairs each; the launcher only starts the kernel if
-// that many fit.
-struct DenseMeta {
-  int* tok;     // LDS [kDenseMeta]: tokens, clamped to [0, B)
-  float* gw;    // LDS [kDenseMeta]
-  int first;    // pair number of entry 0
+// The routing's lists, read with scalar loads: in the loading wavefronts a vector load or an LDS read between the
+// requests would wait for every request before it.
+typedef const __attribute__((address_space(4))) int32_t* scalar_ints;
+struct DenseLists {
+  scalar_ints active, off, tok;
 };
 
-// Where one wavefront finds a job's operands: wave-uniform base addresses (they stay in scalar
-// registers, with the slab's column offset added there) and one 32-bit byte offset per lane and
-// operand kind.  The weight offset is the same for every job.
-struct DenseOperands {
-  const char* a0;   // first row of the wavefront's tile 0
-  const char* a1;   // ... of tile 1: W_up (gate/up stage) or the next 16 rows of W_down
-  uint32_t off_b[kDenseBLoads];  // per lane: its piece of its token rows
-};
-
-__device__ __forceinline__ u32x4_t load_stream_q(const char* base, uint32_t off) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(base + off));
-}
-__device__ __forceinline__ u32x4_t load_plain_q(const char* base, uint32_t off) {
-  return *reinterpret_cast<const u32x4_t*>(base + off);
-}
-
-__device__ __forceinline__ int sgpr(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
+// The first job at or behind pass `pass` of granule u; u1: end of the workgroup's share.
 template <int STAGE>
-__device__ __forceinline__ DenseJob dense_job(const int* l_active, const int* l_off, int u, int pass, int u1, int upe,
+__device__ __forceinline__ DenseJob dense_job(const DenseLists& w, int u, int pass, int u1, int gpe, int N,
                                               int pairs_max) {
-  constexpr int kUnitRows = STAGE == 0 ? 128 : 256;
+  constexpr int kRows = STAGE == 0 ? 16 : 32;
   DenseJob j{};
-  j.valid = false;
-  while (u < u1) {  // experts without usable pairs never occur after a valid routing
-    const int a = u / upe;
-    const int off = sgpr(l_off[a]), cnt = sgpr(l_off[a + 1]) - off;
+  while (u < u1) {
+    const int a = u / gpe;
+    int n = (a + 1) * gpe - u;
+    n = n < u1 - u ? n : u1 - u;
+    const int jobs = (n + kMulWaves - 1) / kMulWaves;
+    n = (n + jobs - 1) / jobs;
+    const int off = w.off[a], cnt = w.off[a + 1] - off;
+    // experts without usable pairs never occur after a valid routing
     if (off >= 0 && cnt > 0 && off + cnt <= pairs_max && pass * kDenseTokens < cnt) {
       j.u = u;
+      j.n = n;
       j.pass = pass;
-      j.e = sgpr(l_active[a]);
-      j.row0 = (u - a * upe) * kUnitRows;
+      const int e = w.active[a];
+      j.e = e < 0 ? 0 : (e >= N ? N - 1 : e);
+      j.row0 = (u - a * gpe) * kRows;
       j.pair0 = off + pass * kDenseTokens;
       const int rem = cnt - pass * kDenseTokens;
       j.cnt = rem < kDenseTokens ? rem : kDenseTokens;
-      j.valid = true;
       return j;
     }
-    ++u;
+    u += n;
     pass = 0;
   }
   return j;
 }
-
 template <int STAGE>
-__device__ __forceinline__ DenseOperands dense_operands(const DenseParams& p, const DenseMeta& mv, const DenseJob& j,
-                                                       int wave, int lane) {
-  constexpr int kWaveRows = STAGE == 0 ? 16 : 32;
-  DenseOperands o;
-  const size_t first = ((size_t)j.e * p.rows + (size_t)(j.row0 + wave * kWaveRows)) * p.L * sizeof(uint16_t);
-  o.a0 = reinterpret_cast<const char*>(p.wa) + first;
-  o.a1 = STAGE == 0 ? reinterpret_cast<const char*>(p.wb) + first : o.a0 + (size_t)16 * p.L * sizeof(uint16_t);
-#pragma unroll
-  for (int h = 0; h < kDenseBLoads; ++h) {
-    const int n = h * 64 + wave * 8 + (lane >> 3);  // a token row this lane helps to load; past the last one: the last again
-    const int nn = n < j.cnt ? n : j.cnt - 1;
-    int pi = j.pair0 + nn;
-    pi = pi < 0 ? 0 : (pi >= p.pairs_max ? p.pairs_max - 1 : pi);
-    const int vrow = STAGE == 0 ? mv.tok[j.mbase + nn] : pi;
-    // below 2^31 by the entry points' limits on B, k, d and I
-    o.off_b[h] = (uint32_t(vrow) * uint32_t(p.L) + (lane & 7) * 8) * uint32_t(sizeof(uint16_t));
-  }
-  return o;
+__device__ __forceinline__ DenseJob dense_next(const DenseJob& j, const DenseLists& w, int u1, int gpe, int N, int pairs_max) {
+  const bool again = (j.pass + 1) * kDenseTokens < w.off[j.u / gpe + 1] - w.off[j.u / gpe];
+  return dense_job<STAGE>(w, again ? j.u : j.u + j.n, again ? j.pass + 1 : 0, u1, gpe, N, pairs_max);
 }
 
-// registers of one slab in flight: four pieces of weight rows (tile 0 rows 0-7, 8-15, tile 1 likewise), one of a token row
-struct DenseSlab {
-  u32x4_t a[4], b[kDenseBLoads];
+// 16 bytes per lane from memory to LDS, lane l's at `lds` (wave-uniform) + 16 l.
+template <int AUX>
+__device__ __forceinline__ void load_to_lds(const char* from, const char* lds) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void*)(from),
+      (__attribute__((address_space(3))) void*)(__attribute__((address_space(3))) char*)(lds), 16, 0, AUX);
+}
+constexpr int kAuxStream = 2;  // non-temporal: weights are read once
+
+// Every wavefront passes the same barriers in the same order (the two roles in code of their own).
+__device__ __forceinline__ void dense_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// ---- the loading wavefronts
+// Wavefront l brings a slab's rows 64 l .. 64 l + 63 of the job's tiles (granules 2 l and 2 l + 1: eight requests, or
+// none past the job's last granule) and token rows 32 l .. 32 l + 31 (four requests, or none).  In LDS a row's eight
+// 16-byte pieces are swapped among themselves by its number (piece c lies at c ^ (row % 8)), which keeps the
+// multiplying wavefronts' reads free of bank conflicts; the request does it by which piece a lane asks for.
+// A workgroup's ring: room for the granules of its largest job and the token rows of its fullest pass, as many slabs
+// as fit.
+struct DenseRing {
+  char* lds;
+  int w32, t32;  // granules and blocks of 32 token rows per slab
+  int slabs;
+  __device__ __forceinline__ char* weights(int slot) const { return lds + slot * (w32 + t32) * kRows32; }
+  __device__ __forceinline__ char* tokens(int slot) const { return weights(slot) + w32 * kRows32; }
+  __device__ __forceinline__ int next(int slot) const { return slot + 1 == slabs ? 0 : slot + 1; }
 };
 
-template <int STAGE>
-__device__ __forceinline__ void dense_request(DenseSlab& r, const DenseParams& p, const DenseOperands& q,
-                                              uint32_t off_a, int slab) {
-  const size_t col = (size_t)slab * kDenseSlab * sizeof(uint16_t);
-  const size_t rows8 = (size_t)8 * p.L * sizeof(uint16_t);
-  r.a[0] = load_stream_q(q.a0 + col, off_a);
-  r.a[1] = load_stream_q(q.a0 + rows8 + col, off_a);
-  r.a[2] = load_stream_q(q.a1 + col, off_a);
-  r.a[3] = load_stream_q(q.a1 + rows8 + col, off_a);
-#pragma unroll
-  for (int h = 0; h < kDenseBLoads; ++h) r.b[h] = load_plain_q(reinterpret_cast<const char*>(p.vec) + col, q.off_b[h]);
-}
-
-// The slab loop of one job with ng token groups.  ring[] holds the slabs in flight (slot = slab % 4).
-// One instance of the loop serves every group count (a branch per group, wave-uniform): with an
-// instance per count the compiler moves the ring between their register assignments from job to
-// job, which waits for every load in flight.
-template <int STAGE>
-__device__ __forceinline__ void dense_run(DenseSlab (&ring)[kDenseLook], const DenseParams& p, const DenseOperands& cur,
-                                          const DenseOperands& nxt, uint32_t off_a, u32x4_t* lds_a, u32x4_t* lds_b,
-                                          f32x4_t (&acc)[kDenseGroups][2], int ng, int wave, int lane) {
-  const int r = lane & 15, q = lane >> 4;
-  const int wrow = lane >> 3, wcol = lane & 7;
-  const int slabs = p.L / kDenseSlab;  // a multiple of kDenseLook (launcher)
-  for (int sl = 0; sl < slabs; sl += kDenseLook) {
-    const bool last = sl + kDenseLook >= slabs;  // refills then belong to the next job
-#pragma unroll
-    for (int s = 0; s < kDenseLook; ++s) {
-      const int buf = s & 1;
-      u32x4_t* const wa_ = lds_a + buf * (2 * 16 * kDenseRowQuads);
-      u32x4_t* const wb_ = lds_b + buf * (kDenseTokens * kDenseRowQuads);
-      wa_[(wrow)*kDenseRowQuads + wcol] = ring[s].a[0];
-      wa_[(wrow + 8) * kDenseRowQuads + wcol] = ring[s].a[1];
-      wa_[(16 + wrow) * kDenseRowQuads + wcol] = ring[s].a[2];
-      wa_[(24 + wrow) * kDenseRowQuads + wcol] = ring[s].a[3];
-#pragma unroll
-      for (int h = 0; h < kDenseBLoads; ++h) wb_[(h * 64 + wave * 8 + wrow) * kDenseRowQuads + wcol] = ring[s].b[h];
-      {  // selected without a branch: the bases are scalars
-        DenseOperands src;
-        src.a0 = last ? nxt.a0 : cur.a0;
-        src.a1 = last ? nxt.a1 : cur.a1;
-#pragma unroll
-        for (int h = 0; h < kDenseBLoads; ++h) src.off_b[h] = last ? nxt.off_b[h] : cur.off_b[h];
-        dense_request<STAGE>(ring[s], p, src, off_a, last ? s : sl + kDenseLook + s);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i2 = 0; i2 < 2; ++i2) {
-        const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, wa_[r * kDenseRowQuads + i2 * 4 + q]);
-        const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, wa_[(16 + r) * kDenseRowQuads + i2 * 4 + q]);
-#pragma unroll
-        for (int c = 0; c < kDenseGroups; ++c) {
-          if (c >= ng) break;
-          const bf16x8_t bv = __builtin_bit_cast(bf16x8_t, wb_[(16 * c + r) * kDenseRowQuads + i2 * 4 + q]);
-          if (STAGE == 0) {  // result tile [weight row][token]: a lane holds four rows of one token
-            acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bv, acc[c][0], 0, 0, 0);
-            acc[c][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bv, acc[c][1], 0, 0, 0);
-          } else {  // [token][weight row]: 16 lanes hold 16 consecutive output coordinates of one token
-            acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, a0, acc[c][0], 0, 0, 0);
-            acc[c][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, a1, acc[c][1], 0, 0, 0);
-          }
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);  // a slot is refilled as soon as it is free, slab by slab
-    }
+// Waits until at most n of this wavefront's requests (a multiple of four) are outstanding.
+__device__ __forceinline__ void wait_outstanding(int n) {
+  switch (n >> 2) {
+#define OEA_CASE(Q)                                               case Q:                                                           asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * Q) : "memory");     break;
+    OEA_CASE(1) OEA_CASE(2) OEA_CASE(3) OEA_CASE(4) OEA_CASE(5) OEA_CASE(6) OEA_CASE(7)
+    OEA_CASE(8) OEA_CASE(9) OEA_CASE(10) OEA_CASE(11) OEA_CASE(12) OEA_CASE(13) OEA_CASE(14)
+#undef OEA_CASE
+    default:
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 }
 
 template <int STAGE>
-__device__ __forceinline__ void dense_store(const DenseParams& p, const DenseMeta& mv, const DenseJob& j,
-                                            const f32x4_t (&acc)[kDenseGroups][2], int wave, int lane) {
-  constexpr int kWaveRows = STAGE == 0 ? 16 : 32;
+__device__ __forceinline__ void dense_load_wave(const DenseParams& p, const DenseLists& w, const DenseRing ring,
+                                                DenseJob j, int u1, int gpe, int l, int lane) {
+  constexpr int kRows = STAGE == 0 ? 16 : 32;
+  const int slabs = p.L / kDenseSlab;
+  const int lr = lane >> 3;                                  // row of a request's eight
+  const uint32_t piece = uint32_t((lane & 7) ^ lr) * 16;     // byte inside its 128
+  const uint32_t row_bytes = uint32_t(p.L) * 2;
+  const uint32_t off_w = uint32_t(lr) * row_bytes + piece;
+  const char *wa0 = nullptr, *wb0 = nullptr;  // first row of granule 2 l in W_gate and W_up, or in W_down
+  uint32_t off_t[4];                          // this lane's pieces of its token rows
+  bool first_half = false, second_half = false, some = false;  // granules 2 l and 2 l + 1 and any of the token rows are in the job
+  auto open = [&]() __attribute__((always_inline)) {
+    first_half = 2 * l < j.n;
+    second_half = 2 * l + 1 < j.n;
+    some = 32 * l < j.cnt;
+    const size_t at = ((size_t)j.e * p.rows + (size_t)(j.row0 + 2 * l * kRows)) * row_bytes;
+    wa0 = reinterpret_cast<const char*>(p.wa) + at;
+    wb0 = reinterpret_cast<const char*>(p.wb) + at;
+    if (!some) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int mine = 0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const int n = 32 * l + 8 * i + r;
+        const int pi = j.pair0 + (n < j.cnt ? n : j.cnt - 1);  // past the last token: the last again
+        const int t = STAGE == 0 ? w.tok[pi] : pi;
+        mine = lr == r ? t : mine;
+      }
+      const int lim = STAGE == 0 ? p.B : p.pairs_max;
+      mine = mine < 0 ? 0 : (mine >= lim ? lim - 1 : mine);
+      // below 2^32 by the entry points' limits on B, k, d and I
+      off_t[i] = uint32_t(mine) * row_bytes + piece;
+    }
+  };
+  // Requests of the next slab, into the next place of the ring.  Which slabs this wavefront had anything to request for
+  // is kept as bits, the latest lowest: the number of requests behind a slab says whether it has landed.
+  // The chip's eight XCDs walk the columns from eight different ones on: all workgroups at one column offset of rows that
+  // lie a power of two apart crowd the same memory channels (gate/up, us, from column 0 / like this: d=4096, I=192, B=200
+  // 88 / 67, B=1000 93 / 72; I=1536, B=160 543 / 510; d=2048, I=768, B=512 139 / 136, B=1000 161 / 153).  Not where the
+  // token rows of the whole batch do not fit an XCD's L2 and many jobs read them: in step the XCDs find in the
+  // memory-side cache what one of them has fetched (d=4096, I=1536: B=600 530 / 543, B=1000 549 / 578; at B=400, which
+  // fits, still 498 / 506).
+  const bool in_step = STAGE == 0 && (long long)p.B * p.L > (2 << 20) && p.rows > 256;
+  const int first_slab = in_step ? 0 : int(blockIdx.x % 8) * slabs / 8;
+  int slab = first_slab, slot = 0, asked = 0;
+  uint32_t had_first = 0, had_second = 0, had_some = 0;
+  auto more = [&]() __attribute__((always_inline)) {
+    if (j.n == 0) return;
+    const uint32_t col = uint32_t(slab) * kRowBytes;
+    char* const to = ring.weights(slot) + l * 2 * kRows32;
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+      if (half ? second_half : first_half) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const char* from = STAGE == 0 ? ((i & 2) ? wb0 : wa0) + (size_t)(half * 16 + (i & 1) * 8) * row_bytes
+                                        : wa0 + (size_t)(half * 32 + i * 8) * row_bytes;
+          load_to_lds<kAuxStream>(from + (off_w + col), to + (half * 4 + i) * 8 * kRowBytes);
+        }
+      }
+    if (some) {
+      char* const to_t = ring.tokens(slot) + l * kRows32;
+      const char* const from = reinterpret_cast<const char*>(p.vec) + col;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_to_lds<0>(from + off_t[i], to_t + i * 8 * kRowBytes);
+    }
+    had_first = had_first * 2 + (first_half ? 1 : 0);
+    had_second = had_second * 2 + (second_half ? 1 : 0);
+    had_some = had_some * 2 + (some ? 1 : 0);
+    slot = ring.next(slot);
+    ++asked;
+    if (++slab == slabs) slab = 0;
+    if (slab == first_slab) {
+      j = dense_next<STAGE>(j, w, u1, gpe, p.N, p.pairs_max);
+      open();
+    }
+  };
+  open();
+  // All but one of the ring's places are requested ahead; barrier g hands slab g over and frees slab g - 1's place.
+  for (int i = 0; i + 1 < ring.slabs; ++i) more();
+  for (int g = 0; g < asked; ++g) {
+    // slab g has landed once nothing but the requests behind it is outstanding
+    const uint32_t behind = (1u << (asked - g - 1)) - 1u;
+    wait_outstanding(4 * (__popc(had_first & behind) + __popc(had_second & behind) + __popc(had_some & behind)));
+    dense_barrier();
+    more();
+  }
+}
+
+// ---- the multiplying wavefronts: wavefront v takes granule v of every job
+template <int STAGE>
+__device__ __forceinline__ void dense_store(const DenseParams& p, const int* l_tok, const float* l_gw, const DenseJob& j,
+                                            const f32x4_t (&acc)[kDenseGroups][2], int v, int lane) {
+  constexpr int kRows = STAGE == 0 ? 16 : 32;
   const int r = lane & 15, q = lane >> 4;
   const int rows = p.rows;
   if (STAGE == 0) {
     // the lane holds rows 4 q .. 4 q + 3 of the gate and the up tile for token r of each group
-    const int row = j.row0 + wave * kWaveRows + 4 * q;
+    const int row = j.row0 + v * kRows + 4 * q;
 #pragma unroll
     for (int c = 0; c < kDenseGroups; ++c) {
       const int n = c * 16 + r;
       if (n < j.cnt) {
-        int pi = j.pair0 + n;
-        pi = pi < 0 ? 0 : (pi >= p.pairs_max ? p.pairs_max - 1 : pi);
         uint16_t hv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -240,53 +270,110 @@ __device__ __forceinline__ void dense_store(const DenseParams& p, const DenseMet
         uint2 packed;
         packed.x = uint32_t(hv[0]) | (uint32_t(hv[1]) << 16);
         packed.y = uint32_t(hv[2]) | (uint32_t(hv[3]) << 16);
-        *reinterpret_cast<uint2*>(p.h_out + (size_t)pi * rows + row) = packed;
+        *reinterpret_cast<uint2*>(p.h_out + (size_t)(j.pair0 + n) * rows + row) = packed;
       }
     }
   } else {
     // the lane holds output coordinate r of both tiles for tokens 4 q .. 4 q + 3 of each group: an
     // atomic instruction adds 64 consecutive bytes to each of four rows of out
-    const int row = j.row0 + wave * kWaveRows + r;
+    const int row = j.row0 + v * kRows + r;
+    int first = 4 * q;
+    asm volatile("" : "+v"(first));  // worked out here, not ahead of all jobs: the registers are the accumulators'
+    const int left = j.cnt - first;
+    const int* const tok = l_tok + first;
+    const float* const gws = l_gw + first;
 #pragma unroll
-    for (int c = 0; c < kDenseGroups; ++c)
+    for (int c = 0; c < kDenseGroups; ++c) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int n = c * 16 + 4 * q + i;
-        if (n < j.cnt) {
-          int pi = j.pair0 + n;
-          pi = pi < 0 ? 0 : (pi >= p.pairs_max ? p.pairs_max - 1 : pi);
-          const int orow = p.per_pair ? pi : mv.tok[j.mbase + n];
-          const float gw = mv.gw[j.mbase + n];
+        if (c * 16 + i < left) {
+          const int orow = p.per_pair ? j.pair0 + first + c * 16 + i : tok[c * 16 + i];
+          const float gw = gws[c * 16 + i];
           float* const o = p.out + (size_t)orow * rows + row;
           unsafeAtomicAdd(o, gw * acc[c][0][i]);
           unsafeAtomicAdd(o + 16, gw * acc[c][1][i]);
         }
       }
+    }
   }
 }
 
 template <int STAGE>
-__global__ __launch_bounds__(kFfnThreads) void expert_dense_kernel(DenseParams p) {
-  extern __shared__ uint4 lds4[];
-  __shared__ int l_active[OEA_MAX_N];
-  __shared__ int l_off[OEA_MAX_N + 1];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int N = p.N;
-  // the lists are read whole beside their length (one round trip to memory instead of two)
-  int T = *p.g.n_active;
-  for (int i = tid; i <= N; i += kFfnThreads) {
-    const int e = p.g.active_list[i < N ? i : N - 1];
-    l_off[i] = p.g.grp_off[i];
-    if (i < N) l_active[i] = e < 0 ? 0 : (e >= N ? N - 1 : e);
+__device__ __forceinline__ void dense_multiply_wave(const DenseParams& p, const DenseLists& w, const DenseRing ring,
+                                                    int* const l_tok, float* const l_gw, DenseJob j, int u1, int gpe, int v, int lane) {
+  const int r = lane & 15, q = lane >> 4;
+  const int slabs = p.L / kDenseSlab;
+  // a lane's piece of a row: columns 8 q .. 8 q + 7 of each of the slab's two steps (see the loading wavefronts)
+  const int at0 = r * kRowBytes + ((q ^ (r & 7)) * 16), at1 = r * kRowBytes + (((4 + q) ^ (r & 7)) * 16);
+  int slot = 0;
+  while (j.n != 0) {
+    const bool mine = v < j.n;
+    const int ng = (j.cnt + 15) >> 4;
+    f32x4_t acc[kDenseGroups][2];
+#pragma unroll
+    for (int c = 0; c < kDenseGroups; ++c) acc[c][0] = acc[c][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // token and gate weight of the job's pairs, for its results: requested now, put into LDS during the last slab
+    int tok = 0;
+    float gw = 0.f;
+    const int n = v * 64 + lane;
+    if (STAGE == 1 && n < j.cnt) {
+      tok = p.g.grp_tok[j.pair0 + n];
+      gw = p.g.grp_gw[j.pair0 + n];
+    }
+    DenseJob nxt{};
+    for (int s = 0; s < slabs; ++s) {
+      dense_barrier();
+      if (s == slabs / 2) nxt = dense_next<STAGE>(j, w, u1, gpe, p.N, p.pairs_max);  // trips to memory, between results no more
+      const char* const wv = ring.weights(slot) + (mine ? v : 0) * kRows32;
+      const char* const tv = ring.tokens(slot);
+      bf16x8_t a[2][2];
+#pragma unroll
+      for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+        for (int tile = 0; tile < 2; ++tile)
+          a[i2][tile] = __builtin_bit_cast(
+              bf16x8_t, *reinterpret_cast<const u32x4_t*>(wv + tile * 16 * kRowBytes + (i2 ? at1 : at0)));
+      if (STAGE == 1 && s == slabs - 1 && n < kDenseTokens) {  // every wavefront has left the previous job behind
+        l_tok[n] = tok < 0 ? 0 : (tok >= p.B ? p.B - 1 : tok);
+        l_gw[n] = gw;
+      }
+      if (mine) {
+#pragma unroll
+        for (int c = 0; c < kDenseGroups; ++c) {
+          if (c >= ng) break;
+#pragma unroll
+          for (int i2 = 0; i2 < 2; ++i2) {
+            const bf16x8_t b = __builtin_bit_cast(
+                bf16x8_t, *reinterpret_cast<const u32x4_t*>(tv + 16 * c * kRowBytes + (i2 ? at1 : at0)));
+            if (STAGE == 0) {  // result tile [weight row][token]: a lane holds four rows of one token
+              acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i2][0], b, acc[c][0], 0, 0, 0);
+              acc[c][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i2][1], b, acc[c][1], 0, 0, 0);
+            } else {  // [token][weight row]: 16 lanes hold 16 consecutive output coordinates of one token
+              acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[i2][0], acc[c][0], 0, 0, 0);
+              acc[c][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[i2][1], acc[c][1], 0, 0, 0);
+            }
+          }
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slab's token rows have been read
+      slot = ring.next(slot);
+    }
+    if (mine) dense_store<STAGE>(p, l_tok, l_gw, j, acc, v, lane);
+    j = nxt;
   }
-  T = T < 0 ? 0 : (T > N ? N : T);
-  __syncthreads();
+}
 
-  // units of this workgroup: a contiguous, equal share of all active experts' row blocks
-  constexpr int kUnitRows = STAGE == 0 ? 128 : 256;
-  const int upe = p.rows / kUnitRows;
-  const long long U = (long long)T * upe;
+template <int STAGE>
+__global__ __launch_bounds__(kDenseThreads) void expert_dense_kernel(DenseParams p) {
+  extern __shared__ uint4 lds4[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const DenseLists w{(scalar_ints)p.g.active_list, (scalar_ints)p.g.grp_off, (scalar_ints)p.g.grp_tok};
+  int T = *(scalar_ints)p.g.n_active;
+  T = T < 0 ? 0 : (T > p.N ? p.N : T);
+  constexpr int kRows = STAGE == 0 ? 16 : 32;
+  const int gpe = p.rows / kRows;
+  const long long U = (long long)T * gpe;
   // Consecutive shares go to workgroups of the same XCD (workgroups are dealt out to the eight in turn), so
   // the units of an expert find its token rows in one L2 instead of fetching them into all eight
   // (B=1000, d=4096, I=1536: gate/up 567 -> 558 us, down 336 -> 328 us; layers up to 2.4 GB of active weights 0 to 2 %).
@@ -294,68 +381,57 @@ __global__ __launch_bounds__(kFfnThreads) void expert_dense_kernel(DenseParams p
   // in turn, us: d=4096, N=128, I=1024 564 / 534 at B=200 and 577 / 557 at B=400, I=1536 813 / 803 at B=200, 818 / 817 at
   // B=400, 856 / 859 at B=640, 893 / 898 at B=800).
   const int G = int(gridDim.x), per_xcd = G / 8;
-  const bool by_xcd = G % 8 == 0 && ((long long)T * p.rows * p.L <= 500000000ll || l_off[T] >= 40 * T);
+  const bool by_xcd = G % 8 == 0 && ((long long)T * p.rows * p.L <= 500000000ll || w.off[T] >= 40 * T);
   const int share = by_xcd ? int(blockIdx.x % 8) * per_xcd + int(blockIdx.x / 8) : int(blockIdx.x);
-  const int u0 = int(U * share / G), u1 = int(U * (share + 1) / G);
-  u32x4_t* const lds_a = reinterpret_cast<u32x4_t*>(lds4) + wave * kDenseLdsA;
-  u32x4_t* const lds_b = reinterpret_cast<u32x4_t*>(lds4) + kFfnWaves * kDenseLdsA;
-
-  DenseJob cur = dense_job<STAGE>(l_active, l_off, u0, 0, u1, upe, p.pairs_max);
-  if (!cur.valid) return;  // uniform over the workgroup
-  // token and gate weight of every pair of this workgroup's experts -> LDS
-  DenseMeta mv{};
-  mv.tok = reinterpret_cast<int*>(lds_b + kDenseLdsB);
-  mv.gw = reinterpret_cast<float*>(mv.tok + kDenseMeta);
+  // Equal shares of whole jobs of m granules, or (m = 1) shares that end anywhere, which makes a job more of most: a
+  // job's slab costs its granules and about three granules' time of its own.  Gate/up and down, us, any / whole: d=2048,
+  // I=768, B=200 142 + 76 / 132 + 72; d=4096, I=1536, B=160 down 272 / 265.
+  int m = 1;
   {
-    const int a_first = u0 / upe, a_last = (u1 - 1) / upe;  // u1 > u0: there is a valid job
-    const int m0 = sgpr(l_off[a_first]), m1 = sgpr(l_off[a_last + 1]);
-    mv.first = m0;
-    // never false after a valid routing (see DenseMeta); keeps the copy inside its LDS area
-    if (!(m0 >= 0 && m1 >= m0 && m1 - m0 <= kDenseMeta && m1 <= p.pairs_max)) return;
-    for (int i = tid; i < m1 - m0; i += kFfnThreads) {
-      const int t = p.g.grp_tok[m0 + i];
-      mv.tok[i] = t < 0 ? 0 : (t >= p.B ? p.B - 1 : t);
-      mv.gw[i] = p.g.grp_gw[m0 + i];
+    const float shares = float(G), most = ceilf(float(U) / shares);
+    float best = most <= 1.f ? 4.f : most + 3.f * (ceilf(most / kMulWaves) + 1.f);
+#pragma unroll
+    for (int c = kMulWaves; c >= 2; --c) {
+      const float cost = ceilf(float(U) * (1.f / c) / shares) * (c + 3.f);
+      if ((p.divisors >> c & 1) && cost < best) {
+        best = cost;
+        m = c;
+      }
     }
   }
-  cur.mbase = cur.pair0 - mv.first;
-  __syncthreads();
-  DenseOperands pc = dense_operands<STAGE>(p, mv, cur, wave, lane);
-  // per lane: row lane / 8 of a group of eight rows, 16-byte piece lane % 8 of the slab's 128 bytes
-  const uint32_t off_a = (uint32_t(lane >> 3) * uint32_t(p.L) + (lane & 7) * 8) * uint32_t(sizeof(uint16_t));
-  DenseSlab ring[kDenseLook];
-#pragma unroll
-  for (int s = 0; s < kDenseLook; ++s) dense_request<STAGE>(ring[s], p, pc, off_a, s);
-  while (cur.valid) {
-    // the job after this one; without one the last refills read this job's first slabs again (unused)
-    DenseJob nxt = dense_job<STAGE>(l_active, l_off, cur.u, cur.pass + 1, u1, upe, p.pairs_max);
-    nxt.mbase = nxt.pair0 - mv.first;
-    const DenseOperands pn = nxt.valid ? dense_operands<STAGE>(p, mv, nxt, wave, lane) : pc;
-    f32x4_t acc[kDenseGroups][2];
-#pragma unroll
-    for (int c = 0; c < kDenseGroups; ++c) acc[c][0] = acc[c][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    dense_run<STAGE>(ring, p, pc, pn, off_a, lds_a, lds_b, acc, (cur.cnt + 15) >> 4, wave, lane);
-    dense_store<STAGE>(p, mv, cur, acc, wave, lane);
-    cur = nxt;
-    pc = pn;
+  const int u0 = int(U / m * share / G) * m, u1 = int(U / m * (share + 1) / G) * m;
+  const DenseJob first = dense_job<STAGE>(w, u0, 0, u1, gpe, p.N, p.pairs_max);
+  if (first.n == 0) return;  // uniform over the workgroup
+  DenseRing ring{reinterpret_cast<char*>(lds4), gpe < u1 - u0 ? gpe : u1 - u0, 1, 0};
+  ring.w32 = ring.w32 < kMulWaves ? ring.w32 : kMulWaves;
+  for (int a = u0 / gpe; a <= (u1 - 1) / gpe; ++a) {
+    const int t32 = (w.off[a + 1] - w.off[a] + 31) / 32;
+    ring.t32 = t32 > ring.t32 ? t32 : ring.t32;
   }
+  ring.t32 = ring.t32 < kDenseTokens / 32 ? ring.t32 : kDenseTokens / 32;
+  ring.slabs = kRingBytes / ((ring.w32 + ring.t32) * kRows32);
+  ring.slabs = ring.slabs < kMaxRing ? ring.slabs : kMaxRing;
+  int* const l_tok = reinterpret_cast<int*>(ring.lds + kRingBytes);
+  float* const l_gw = reinterpret_cast<float*>(l_tok + kDenseTokens);
+  if (wave < kMulWaves)
+    dense_multiply_wave<STAGE>(p, w, ring, l_tok, l_gw, first, u1, gpe, wave, lane);
+  else
+    dense_load_wave<STAGE>(p, w, ring, first, u1, gpe, wave - kMulWaves, lane);
 }
 
 }  // namespace
 
 // One expert stage (0 gate/up, 1 down) on the matrix cores; hipErrorNotSupported for storage types
-// and shapes it is not built for (bf16; rows a multiple of a workgroup's unit, inner dimension of 256).
+// and shapes it is not built for (bf16; rows a multiple of a granule, inner dimension of a slab).
 hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, const void* wb, void* h_out, float* out,
                                   int B, int d, int N, int I, int k, oea_dtype dt, Grouping g, bool per_pair,
                                   hipStream_t s) {
-  if (dt != OEA_BF16 || N > OEA_MAX_N) return hipErrorNotSupported;
+  static_assert(kDenseSlab == 64, "dense_stage_fits");
+  if (!dense_stage_fits(stage, d, N, I, dt)) return hipErrorNotSupported;
   const int rows = stage == 0 ? I : d, L = stage == 0 ? d : I;
-  if (rows % (stage == 0 ? 128 : 256) != 0 || L % (kDenseLook * kDenseSlab) != 0) return hipErrorNotSupported;
   int dev = 0, grid = 0;
   if (!current_device(&dev, &grid)) return hipErrorUnknown;
   if (grid < 1) return hipErrorNotSupported;
-  // the pairs of the experts one workgroup can touch must fit its LDS copy of their tokens and weights
-  if (((long long)(N + grid - 1) / grid + 1) * B > kDenseMeta) return hipErrorNotSupported;
   DenseParams p{};
   p.wa = static_cast<const uint16_t*>(wa);
   p.wb = static_cast<const uint16_t*>(wb);
@@ -369,15 +445,17 @@ hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, co
   p.B = B;
   p.pairs_max = B * k;
   p.per_pair = per_pair ? 1 : 0;
+  for (int c = 2; c <= kMulWaves; ++c)
+    if (rows / (stage == 0 ? 16 : 32) % c == 0) p.divisors |= 1 << c;
   static PerDevice attr0, attr1;
   const void* kern = stage == 0 ? reinterpret_cast<const void*>(expert_dense_kernel<0>)
                                 : reinterpret_cast<const void*>(expert_dense_kernel<1>);
   hipError_t e = ensure_dynamic_lds(kern, (int)kDenseLdsBytes, stage == 0 ? attr0 : attr1);
   if (e != hipSuccess) return e;
   if (stage == 0)
-    hipLaunchKernelGGL(expert_dense_kernel<0>, dim3(grid), dim3(kFfnThreads), kDenseLdsBytes, s, p);
+    hipLaunchKernelGGL(expert_dense_kernel<0>, dim3(grid), dim3(kDenseThreads), kDenseLdsBytes, s, p);
   else
-    hipLaunchKernelGGL(expert_dense_kernel<1>, dim3(grid), dim3(kFfnThreads), kDenseLdsBytes, s, p);
+    hipLaunchKernelGGL(expert_dense_kernel<1>, dim3(grid), dim3(kDenseThreads), kDenseLdsBytes, s, p);
   return hipGetLastError();
 }
 

@@ -195,6 +195,14 @@ hipError_t try_launch_stage_kernels(int stage, const void* vec, const void* wa, 
                                     float* out, int B, int d, int N, int I, int k, oea_dtype dt, Grouping g,
                                     bool per_pair, hipStream_t s);
 
+// the layer shapes that the single kernel is built for
+inline bool fused_kernel_shape(int d, int I) { return (d == 2048 && I == 768) || (d == 4096 && I == 1536); }
+// the stages that the matrix-core kernel is built for: whole granules of rows, whole slabs of the inner dimension
+inline bool dense_stage_fits(int stage, int d, int N, int I, oea_dtype dt) {
+  const int rows = stage == 0 ? I : d, L = stage == 0 ? d : I;
+  return dt == OEA_BF16 && N <= OEA_MAX_N && rows % (stage == 0 ? 16 : 32) == 0 && L % 64 == 0;
+}
+
 // one expert stage (0 gate/up, 1 down) on the matrix cores, for batches in which experts serve many tokens
 hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, const void* wb, void* h_out,
                                   float* out, int B, int d, int N, int I, int k, oea_dtype dt, Grouping g,

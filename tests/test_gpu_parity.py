@@ -1200,3 +1200,29 @@ def test_bounded_waits_report_a_timeout(torch, B_, oracle):
     ref = oracle.moe_decode(L.x, L.w_router, L.w_gate, L.w_up, L.w_down, L.k, 2)
     for got in (good, again):
         assert np.abs(got - ref["out"]).max() / np.abs(ref["out"]).max() <= TOL[L.dtype]
+
+
+@pytest.mark.parametrize("shape", [
+    # rows that are no multiple of a workgroup's eight granules, inner dimensions of one, three and five slabs, a granule
+    # count without a divisor below nine; one pair per expert; more tokens on an expert than a pass holds
+    (130, 64, 24, 64, 4, 2, False), (129, 192, 40, 320, 3, 1, False), (200, 576, 6, 176 * 4, 2, 2, True),
+    (150, 320, 512, 192, 1, 1, False), (640, 128, 3, 64, 2, 1, True)],
+    ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d%s" % (c[:6] + ("-det" if c[6] else "",)))
+def test_matrix_core_granules(torch, B_, oracle, shape):
+    """The matrix-core stages where a job has fewer granules or slabs than the ring and the wavefronts could take."""
+    B, d, N, I, k, k0, det = shape
+    L = W.make_layer("toy", 1700 + B, d=d, I=I, N=N, B=B, k=k, dtype="bf16")
+    mask = np.ones(B, np.uint8)
+    mask[B // 2] = 0
+    ws = B_.new_workspace(B, d, N, I, k, deterministic=det)
+    dev = {f: B_.to_device(getattr(L, f)) for f in ("x", "w_router", "w_gate", "w_up", "w_down")}
+    assert expert_kernels(torch, B_, dev, k, k0, ws, 4, det) == [4, 4]
+    outs = []
+    for _ in range(2):
+        out, tap = B_.moe_decode(dev["x"], dev["w_router"], dev["w_gate"], dev["w_up"], dev["w_down"], k, k0, ws, taps=True,
+                                 token_mask=torch.from_numpy(mask).cuda(), deterministic=det, kernel_path=4)
+        torch.cuda.synchronize()
+        outs.append(out.cpu().numpy())
+        check_layer(oracle, L, k0, outs[-1], {n: v.cpu().numpy() for n, v in tap.items()}, str(shape), mask=mask)
+    if det:
+        assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
