@@ -1,6 +1,7 @@
 // C ABI of liboea: argument checks, workspace carving, kernel enqueue.  See include/oea.h.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <mutex>
 
 #include "oea_internal.h"
@@ -45,11 +46,35 @@ static int check_route_sizes(int B, int N, int k, int k0) {
   return OEA_OK;
 }
 
-// Batches above this run their expert stages on the matrix cores (three-kernel path); it is the end of the single
-// kernel's range.  On a fixed batch of 128 tokens the single kernel leads on the 30B shape (213 against 229 us), with
-// batches that change from call to call it leads up to B = 96 (204 / 212; B=128: 236 / 224), on the 235B
-// shape up to B = 64 (615 / 634; B=96: 770 / 742, B=128: 1062 / 782).
-static constexpr int kDenseFromBatch = 128;
+// Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
+// batches at the sizes that it is built for, else where an active expert serves enough pairs.  The number of active
+// experts is the one that B independent choices of k0 among N give (a batch of similar tokens has fewer, and more pairs
+// on each).  Measured with token batches that change from call to call, us, other kernels / matrix cores:
+//   single kernel, d=2048, I=768, N=128, k=8   k0=3: 5.1 pairs 177 / 187 (B=64), 5.9 198 / 197, 6.7 213 / 211,
+//                                               7.5 234 / 215, 8.4 240 / 227 (B=128); k0=1: 11.4 167 / 144; k0=8: 6.0 232 / 237
+//   single kernel, d=4096, I=1536, N=128, k=8  k0=3: 3.9 435 / 440 (B=32), 4.4 556 / 552, 5.1 646 / 631, 5.9 712 / 683,
+//                                               8.4 1102 / 789 (B=128); k0=1: 10 440 / 345; k0=8: 4.1 784 / 783
+//   dot-product kernels (the better of streaming and stage kernels)
+//                  d=4096, I=192, N=128, k0=3  3.0 56 / 60 (B=16), 3.4 72 / 70, 4.4 107 / 101, 5.1 125 / 109, 8.5 187 / 133 (B=130)
+//                  d=512, I=512, N=60, k0=3    3.2 31 / 27 (B=9), 5.6 46 / 33;  d=512, I=192, N=64  3.1 29 / 26 (B=32), 8.3 48 / 34
+//                  d=1024, I=256, N=24         4.9 29 / 27 (B=9), 12 40 / 30;   d=64, I=64, N=16    3.2 23 / 22 (B=9), 17 40 / 24
+//                  d=2048, I=1024, N=160, k0=1 1.8 85 / 82 (B=32), 2.4 145 / 148, 2.9 213 / 210
+static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool masked, bool deterministic) {
+  if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
+  const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
+  double pairs = double(B) * (k < active ? k : active) / active;  // a token has at most the active ones
+  if (masked) pairs *= 0.7;  // some of the tokens are padding (B=126, 72 live, d=2048, I=768, k0=8: 212 / 222)
+  if (!fused_kernel_shape(d, I)) {
+    // few experts with long rows: a workgroup's walk over the slabs (about 0.45 us each) outlasts what the other kernels
+    // need for the weights (5.5 TB/s) and the pairs (d=4096, I=192, k0=2: B=8 42 / 48, B=12 48 / 55; d=1024, I=256,
+    // k0=1: B=4 24 / 27, B=12 31 / 28; d=2048, I=1024, k0=1: B=6 43 / 45, B=8 50 / 45)
+    const double walk = 0.45 * (d + I) / 64, other = active * 6.0 * d * I / 5.5e6 + 1.2 * pairs;
+    return B > 4 && pairs >= 3.2 && walk <= other;
+  }
+  if (deterministic) return false;  // the single kernel gives a token the same bits in every batch
+  // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
+  return d == 4096 ? B >= 48 && pairs >= 5.0 : B > 64 && pairs >= 9.0;
+}
 
 // Stages with little work per wavefront keep the streaming kernels with fixed shares: the stage kernels' share by
 // cost, result buffer and pair lists cost 1 to 2.5 us, and what they save is the pairs' work that fixed shares
@@ -259,7 +284,10 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   };
   if (!mark(0)) return OEA_ERR_HIP;
   hipError_t e = hipErrorNotSupported;
-  if (path == 0)
+  // (above B = 128 a stage that fits runs on the matrix cores even if the other does not)
+  const bool dense_fits = dense_stage_fits(0, d, N, I, dt) && dense_stage_fits(1, d, N, I, dt);
+  const bool dense = path == 4 || (path == 0 && (dense_fits || B > 128) && prefer_matrix_cores(B, d, N, I, k, k0, ex && ex->token_mask, y != nullptr));
+  if (path == 0 && !dense)
     e = try_launch_fused(x, W_router, W_gate, W_up, W_down, ex ? ex->router_bias : nullptr,
                          ex ? ex->token_mask : nullptr, out, logits, h, ro,
                          reinterpret_cast<uint32_t*>(ws + w.ctrl), B, d, N, I, k, k0, dt, s,
@@ -279,8 +307,6 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
     const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, k0, I, d, elem_bytes_of(dt)));
     const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, k0, d, I, elem_bytes_of(dt)));
     const bool generic_only = path == 1;
-    // matrix cores once an expert serves many tokens: above the single kernel's batch range
-    const bool dense = path == 4 || (path == 0 && B > kDenseFromBatch);
     report(0, 4);
     e = dense ? try_launch_dense_stage(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s)
               : hipErrorNotSupported;

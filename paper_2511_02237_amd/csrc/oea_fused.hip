@@ -1297,8 +1297,8 @@ hipError_t try_launch_fused(const void* x, const void* w_router, const void* w_g
                             int k, int k0, oea_dtype dt, hipStream_t s, uint32_t spin_limit, bool cooperative,
                             float* y_per_pair, const RouteGeneralArgs* general) {
   if (dt != OEA_BF16 || N > 128 || B > 128 || k > 16) return hipErrorNotSupported;
-  const bool shape30 = d == 2048 && I == 768, shape235 = d == 4096 && I == 1536;
-  if (!shape30 && !shape235) return hipErrorNotSupported;
+  if (!fused_kernel_shape(d, I)) return hipErrorNotSupported;
+  const bool shape30 = d == 2048;
   int dev = 0, grid = 0;
   if (!current_device(&dev, &grid)) return hipErrorUnknown;
   if (grid < 1) return hipErrorNotSupported;

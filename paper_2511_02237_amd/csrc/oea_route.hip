@@ -7,7 +7,9 @@ namespace oea {
 namespace {
 
 constexpr int kRouteThreads = 1024;
-constexpr int kWideFromBatch = 128;  // larger batches route over many workgroups (see wide_logits_kernel)
+// Larger batches route over many workgroups (see wide_logits_kernel): layer, us, one workgroup / many, d=2048, N=128:
+// B=64 187 / 190, B=96 211 / 210, B=112 215 / 210, B=128 227 / 221; d=512, N=64: B=64 35 / 41.
+constexpr int kWideFromBatch = 96;
 
 // One workgroup routes one decode position (blockIdx.x): its B rows of logits and its own output slices.
 // Positions are independent (Section 4: every position and layer is routed separately), so a grid
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kRouteThreads) void router_route_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batches above 128 tokens: router and routing over many workgroups, as four kernels in stream
+// Batches above 96 tokens: router and routing over many workgroups, as four kernels in stream
 // order (a kernel boundary is the grid-wide synchronisation Algorithm 1 needs twice: the union of
 // Phase 1 before Phase 2, all pair counts before the grouped lists).  The union and the counts live
 // in control words of the workspace that the first kernel clears.  With one workgroup per expert
