@@ -12,10 +12,11 @@
 // granules of one expert against up to 128 of its tokens (an expert with more takes further passes over
 // the same rows), walking the inner dimension in slabs of 64 columns.  Its twelve wavefronts have two roles:
 //   * Four load: every operand goes from memory straight into LDS (global_load_lds, 16 bytes per lane, whole
-//     128-byte row pieces per 8 lanes), two to five slabs ahead of their use, across jobs.  Loads are all that their memory counter counts, so waiting for the oldest slab never
-//     waits for anything else.
-//   * Eight multiply, a granule each.  Their results leave the registers directly at the end of a job: silu(gate) * up rounded to the storage type into h, or gate-weighted atomic adds into
-//     out (Eq. 1).  These stores and adds are in no one's way.
+//     128-byte row pieces per 8 lanes), two to five slabs ahead of their use, across jobs; the tokens and gate weights of
+//     a job's pairs come with its last slab (down stage).  Loads are all that their memory counter counts, so waiting
+//     for the oldest slab never waits for anything else.
+//   * Eight multiply, a granule each, and load nothing.  Their results leave the registers directly at the end of a job:
+//     silu(gate) * up rounded to the storage type into h, or gate-weighted atomic adds into out (Eq. 1).
 // One workgroup barrier per slab orders the two: the slab has landed, the slab before it is used up.
 //
 // Bound by the weight stream: a loop of these requests alone reaches 7.0 TB/s with two slabs of 32 KB in flight per
@@ -32,6 +33,7 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kDenseGroups = 8;     // groups of 16 tokens per pass
 constexpr int kDenseTokens = 16 * kDenseGroups;
@@ -43,7 +45,8 @@ constexpr int kDenseThreads = 64 * (kMulWaves + kLoadWaves);
 constexpr int kRowBytes = kDenseSlab * 2;                  // of a slab in LDS
 constexpr int kRows32 = 32 * kRowBytes;                    // a granule's rows (16 + 16 in the gate/up stage), or 32 token rows
 constexpr int kRingBytes = 3 * (kMulWaves + kDenseTokens / 32) * kRows32;  // three of the largest slabs
-constexpr size_t kDenseLdsBytes = (size_t)kRingBytes + (size_t)kDenseTokens * 8;
+constexpr int kPairBytes = kDenseTokens * 8;               // token and gate weight of a job's pairs, one copy per place of the ring
+constexpr size_t kDenseLdsBytes = (size_t)kRingBytes + (size_t)kMaxRing * kPairBytes;
 
 struct DenseParams {
   const uint16_t* wa;   // gate/up stage: W_gate; down stage: W_down   [N, rows, L]
@@ -112,12 +115,15 @@ __device__ __forceinline__ DenseJob dense_next(const DenseJob& j, const DenseLis
   return dense_job<STAGE>(w, again ? j.u : j.u + j.n, again ? j.pass + 1 : 0, u1, gpe, N, pairs_max);
 }
 
-// 16 bytes per lane from memory to LDS, lane l's at `lds` (wave-uniform) + 16 l.
-template <int AUX>
+// 16 bytes per lane from memory to LDS, lane l's at `lds` (wave-uniform) + 16 l; with WORD 4 bytes, at 4 l.
+template <int AUX, bool WORD = false>
 __device__ __forceinline__ void load_to_lds(const char* from, const char* lds) {
-  __builtin_amdgcn_global_load_lds(
-      (const __attribute__((address_space(1))) void*)(from),
-      (__attribute__((address_space(3))) void*)(__attribute__((address_space(3))) char*)(lds), 16, 0, AUX);
+  const auto src = (const __attribute__((address_space(1))) void*)(from);
+  const auto dst = (__attribute__((address_space(3))) void*)(__attribute__((address_space(3))) char*)(lds);
+  if constexpr (WORD)
+    __builtin_amdgcn_global_load_lds(src, dst, 4, 0, AUX);
+  else
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, AUX);
 }
 constexpr int kAuxStream = 2;  // non-temporal: weights are read once
 
@@ -141,6 +147,8 @@ struct DenseRing {
   int slabs;
   __device__ __forceinline__ char* weights(int slot) const { return lds + slot * (w32 + t32) * kRows32; }
   __device__ __forceinline__ char* tokens(int slot) const { return weights(slot) + w32 * kRows32; }
+  // down stage: the pairs of the job whose last slab is in this place, 32 tokens then 32 gate weights at a time
+  __device__ __forceinline__ char* pairs(int slot) const { return lds + kRingBytes + slot * kPairBytes; }
   __device__ __forceinline__ int next(int slot) const { return slot + 1 == slabs ? 0 : slot + 1; }
 };
 
@@ -206,6 +214,17 @@ __device__ __forceinline__ void dense_load_wave(const DenseParams& p, const Dens
   uint32_t had_first = 0, had_second = 0, had_some = 0;
   auto more = [&]() __attribute__((always_inline)) {
     if (j.n == 0) return;
+    const int next_slab = slab + 1 == slabs ? 0 : slab + 1;
+    if (STAGE == 1 && some && next_slab == first_slab) {
+      // With the job's last slab come the tokens and gate weights of its pairs: that slab's barrier hands them over, and
+      // their place is requested again only behind the next barrier, which the multiplying wavefronts reach with
+      // their results written.  (Not counted below: a wait for a slab before this one then waits for one request too
+      // many.)
+      const int n = 32 * l + (lane & 31);
+      const int pi = j.pair0 + (n < j.cnt ? n : j.cnt - 1);
+      const char* const list = lane < 32 ? reinterpret_cast<const char*>(p.g.grp_tok) : reinterpret_cast<const char*>(p.g.grp_gw);
+      load_to_lds<0, true>(list + (size_t)pi * 4, ring.pairs(slot) + l * 256);
+    }
     const uint32_t col = uint32_t(slab) * kRowBytes;
     char* const to = ring.weights(slot) + l * 2 * kRows32;
 #pragma unroll
@@ -229,7 +248,7 @@ __device__ __forceinline__ void dense_load_wave(const DenseParams& p, const Dens
     had_some = had_some * 2 + (some ? 1 : 0);
     slot = ring.next(slot);
     ++asked;
-    if (++slab == slabs) slab = 0;
+    slab = next_slab;
     if (slab == first_slab) {
       j = dense_next<STAGE>(j, w, u1, gpe, p.N, p.pairs_max);
       open();
@@ -249,7 +268,7 @@ __device__ __forceinline__ void dense_load_wave(const DenseParams& p, const Dens
 
 // ---- the multiplying wavefronts: wavefront v takes granule v of every job
 template <int STAGE>
-__device__ __forceinline__ void dense_store(const DenseParams& p, const int* l_tok, const float* l_gw, const DenseJob& j,
+__device__ __forceinline__ void dense_store(const DenseParams& p, const char* pairs, const DenseJob& j,
                                             const f32x4_t (&acc)[kDenseGroups][2], int v, int lane) {
   constexpr int kRows = STAGE == 0 ? 16 : 32;
   const int r = lane & 15, q = lane >> 4;
@@ -280,15 +299,19 @@ __device__ __forceinline__ void dense_store(const DenseParams& p, const int* l_t
     int first = 4 * q;
     asm volatile("" : "+v"(first));  // worked out here, not ahead of all jobs: the registers are the accumulators'
     const int left = j.cnt - first;
-    const int* const tok = l_tok + first;
-    const float* const gws = l_gw + first;
+    const char* const mine = pairs + first * 4;
 #pragma unroll
     for (int c = 0; c < kDenseGroups; ++c) {
+      // the four tokens' entries at once (those past the last pair are bytes of the place, unused)
+      const char* const entry = mine + (c >> 1) * 256 + (c & 1) * 64;
+      const i32x4_t tok = *reinterpret_cast<const i32x4_t*>(entry);
+      const f32x4_t gws = *reinterpret_cast<const f32x4_t*>(entry + 128);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (c * 16 + i < left) {
-          const int orow = p.per_pair ? j.pair0 + first + c * 16 + i : tok[c * 16 + i];
-          const float gw = gws[c * 16 + i];
+          const int t = tok[i] < 0 ? 0 : (tok[i] >= p.B ? p.B - 1 : tok[i]);
+          const int orow = p.per_pair ? j.pair0 + first + c * 16 + i : t;
+          const float gw = gws[i];
           float* const o = p.out + (size_t)orow * rows + row;
           unsafeAtomicAdd(o, gw * acc[c][0][i]);
           unsafeAtomicAdd(o + 16, gw * acc[c][1][i]);
@@ -300,7 +323,7 @@ __device__ __forceinline__ void dense_store(const DenseParams& p, const int* l_t
 
 template <int STAGE>
 __device__ __forceinline__ void dense_multiply_wave(const DenseParams& p, const DenseLists& w, const DenseRing ring,
-                                                    int* const l_tok, float* const l_gw, DenseJob j, int u1, int gpe, int v, int lane) {
+                                                    DenseJob j, int u1, int gpe, int v, int lane) {
   const int r = lane & 15, q = lane >> 4;
   const int slabs = p.L / kDenseSlab;
   // a lane's piece of a row: columns 8 q .. 8 q + 7 of each of the slab's two steps (see the loading wavefronts)
@@ -312,14 +335,7 @@ __device__ __forceinline__ void dense_multiply_wave(const DenseParams& p, const 
     f32x4_t acc[kDenseGroups][2];
 #pragma unroll
     for (int c = 0; c < kDenseGroups; ++c) acc[c][0] = acc[c][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // token and gate weight of the job's pairs, for its results: requested now, put into LDS during the last slab
-    int tok = 0;
-    float gw = 0.f;
-    const int n = v * 64 + lane;
-    if (STAGE == 1 && n < j.cnt) {
-      tok = p.g.grp_tok[j.pair0 + n];
-      gw = p.g.grp_gw[j.pair0 + n];
-    }
+    const char* pairs = nullptr;
     DenseJob nxt{};
     for (int s = 0; s < slabs; ++s) {
       dense_barrier();
@@ -333,10 +349,6 @@ __device__ __forceinline__ void dense_multiply_wave(const DenseParams& p, const 
         for (int tile = 0; tile < 2; ++tile)
           a[i2][tile] = __builtin_bit_cast(
               bf16x8_t, *reinterpret_cast<const u32x4_t*>(wv + tile * 16 * kRowBytes + (i2 ? at1 : at0)));
-      if (STAGE == 1 && s == slabs - 1 && n < kDenseTokens) {  // every wavefront has left the previous job behind
-        l_tok[n] = tok < 0 ? 0 : (tok >= p.B ? p.B - 1 : tok);
-        l_gw[n] = gw;
-      }
       if (mine) {
 #pragma unroll
         for (int c = 0; c < kDenseGroups; ++c) {
@@ -356,9 +368,10 @@ __device__ __forceinline__ void dense_multiply_wave(const DenseParams& p, const 
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slab's token rows have been read
+      pairs = ring.pairs(slot);
       slot = ring.next(slot);
     }
-    if (mine) dense_store<STAGE>(p, l_tok, l_gw, j, acc, v, lane);
+    if (mine) dense_store<STAGE>(p, pairs, j, acc, v, lane);
     j = nxt;
   }
 }
@@ -411,10 +424,8 @@ __global__ __launch_bounds__(kDenseThreads) void expert_dense_kernel(DenseParams
   ring.t32 = ring.t32 < kDenseTokens / 32 ? ring.t32 : kDenseTokens / 32;
   ring.slabs = kRingBytes / ((ring.w32 + ring.t32) * kRows32);
   ring.slabs = ring.slabs < kMaxRing ? ring.slabs : kMaxRing;
-  int* const l_tok = reinterpret_cast<int*>(ring.lds + kRingBytes);
-  float* const l_gw = reinterpret_cast<float*>(l_tok + kDenseTokens);
   if (wave < kMulWaves)
-    dense_multiply_wave<STAGE>(p, w, ring, l_tok, l_gw, first, u1, gpe, wave, lane);
+    dense_multiply_wave<STAGE>(p, w, ring, first, u1, gpe, wave, lane);
   else
     dense_load_wave<STAGE>(p, w, ring, first, u1, gpe, wave - kMulWaves, lane);
 }

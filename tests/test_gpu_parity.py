@@ -1226,3 +1226,32 @@ def test_matrix_core_granules(torch, B_, oracle, shape):
         check_layer(oracle, L, k0, outs[-1], {n: v.cpu().numpy() for n, v in tap.items()}, str(shape), mask=mask)
     if det:
         assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["atomics", "det"])
+@pytest.mark.parametrize("shape", [
+    # one, two and three slabs of the down stage's inner dimension, with 4 to 40 of its granules per workgroup (jobs of
+    # up to eight, of different experts); few pairs per expert, full groups of 16 and a rest, several passes
+    (16, 2048, 128, 64, 8, 3), (200, 2048, 160, 64, 8, 8), (300, 2048, 96, 128, 6, 2), (130, 4096, 64, 192, 8, 3),
+    (700, 8192, 4, 64, 2, 2)],
+    ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d" % c)
+def test_matrix_core_results_of_consecutive_jobs(torch, B_, oracle, shape, det):
+    """The down stage where a workgroup walks several jobs of several wavefronts each, of different experts or passes, one
+    to three slabs apart: every job's results carry the tokens and gate weights of its own pairs."""
+    B, d, N, I, k, k0 = shape
+    L = W.make_layer("toy", 2900 + B, d=d, I=I, N=N, B=B, k=k, dtype="bf16")
+    ws = B_.new_workspace(B, d, N, I, k, deterministic=det)
+    dev = {f: B_.to_device(getattr(L, f)) for f in ("x", "w_router", "w_gate", "w_up", "w_down")}
+    assert expert_kernels(torch, B_, dev, k, k0, ws, 4, det) == [4, 4]
+    for call in range(3):
+        out, tap = B_.moe_decode(dev["x"], dev["w_router"], dev["w_gate"], dev["w_up"], dev["w_down"], k, k0, ws, taps=True,
+                                 deterministic=det, kernel_path=4)
+        torch.cuda.synchronize()
+        out = out.cpu().numpy()
+        if call == 0:
+            first = out
+            check_layer(oracle, L, k0, out, {n: v.cpu().numpy() for n, v in tap.items()}, str(shape))
+        elif det:
+            assert np.array_equal(out.view(np.uint32), first.view(np.uint32)), "call %d differs" % call
+        else:  # fp32 sums of k products in another order
+            assert np.abs(out - first).max() <= 2e-6 * k * np.abs(first).max(), "call %d" % call
