@@ -49,7 +49,9 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 // Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
 // batches at the sizes that it is built for, else where an active expert serves enough pairs.  The number of active
 // experts is the one that B independent choices of k0 among N give (a batch of similar tokens has fewer, and more pairs
-// on each).  Measured with token batches that change from call to call, us, other kernels / matrix cores:
+// on each).  With the deterministic combine the line is B = 128 alone: below it the kernels give a token the same bits in
+// every batch (above a handful of tokens, where small stages change kernels), above it the matrix cores do.
+// Measured with token batches that change from call to call, us, other kernels / matrix cores:
 //   single kernel, d=2048, I=768, N=128, k=8   k0=3: 5.1 pairs 177 / 187 (B=64), 5.9 198 / 197, 6.7 213 / 211,
 //                                               7.5 234 / 215, 8.4 240 / 227 (B=128); k0=1: 11.4 167 / 144; k0=8: 6.0 232 / 237
 //   single kernel, d=4096, I=1536, N=128, k=8  k0=3: 3.9 435 / 440 (B=32), 4.4 556 / 552, 5.1 646 / 631, 5.9 712 / 683,
@@ -60,6 +62,7 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 //                  d=1024, I=256, N=24         4.9 29 / 27 (B=9), 12 40 / 30;   d=64, I=64, N=16    3.2 23 / 22 (B=9), 17 40 / 24
 //                  d=2048, I=1024, N=160, k0=1 1.8 85 / 82 (B=32), 2.4 145 / 148, 2.9 213 / 210
 static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool masked, bool deterministic) {
+  if (deterministic) return B > 128;
   if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
   const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
   double pairs = double(B) * (k < active ? k : active) / active;  // a token has at most the active ones
@@ -71,7 +74,6 @@ static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool 
     const double walk = 0.45 * (d + I) / 64, other = active * 6.0 * d * I / 5.5e6 + 1.2 * pairs;
     return B > 4 && pairs >= 3.2 && walk <= other;
   }
-  if (deterministic) return false;  // the single kernel gives a token the same bits in every batch
   // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
   return d == 4096 ? B >= 48 && pairs >= 5.0 : B > 64 && pairs >= 9.0;
 }
@@ -302,13 +304,13 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   } else {
     e = launch_router_and_route(x, W_router, ex ? ex->router_bias : nullptr, ex ? ex->token_mask : nullptr, B, d,
                                 N, k, k0, dt, logits, y ? y : out, y ? (size_t)B * k * d : (size_t)B * d,
-                                reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, general ? &ga : nullptr, s);
+                                reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, general ? &ga : nullptr, y != nullptr, s);
     if (e != hipSuccess || !mark(1) || !mark(2)) return OEA_ERR_HIP;
     const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, k0, I, d, elem_bytes_of(dt)));
     const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, k0, d, I, elem_bytes_of(dt)));
     const bool generic_only = path == 1;
     report(0, 4);
-    e = dense ? try_launch_dense_stage(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, false, s)
+    e = dense ? try_launch_dense_stage(0, x, W_gate, W_up, h, nullptr, B, d, N, I, k, dt, g, y != nullptr, s)
               : hipErrorNotSupported;
     if (e == hipErrorNotSupported && gate_up_stage) {
       report(0, 3);

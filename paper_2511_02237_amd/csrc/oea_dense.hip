@@ -56,7 +56,7 @@ struct DenseParams {
   float* out;           // down stage: out [B, rows] (or [pairs, rows], one row per pair)
   Grouping g;
   int rows, L, N, B, pairs_max;
-  int per_pair;
+  int deterministic;  // a row of `out` per pair (down stage), and every sum in one order (see the slabs' start)
   int divisors;  // bit c: an expert's granules are a multiple of c
 };
 
@@ -207,8 +207,9 @@ __device__ __forceinline__ void dense_load_wave(const DenseParams& p, const Dens
   // 88 / 67, B=1000 93 / 72; I=1536, B=160 543 / 510; d=2048, I=768, B=512 139 / 136, B=1000 161 / 153).  Not where the
   // token rows of the whole batch do not fit an XCD's L2 and many jobs read them: in step the XCDs find in the
   // memory-side cache what one of them has fetched (d=4096, I=1536: B=600 530 / 543, B=1000 549 / 578; at B=400, which
-  // fits, still 498 / 506).
-  const bool in_step = STAGE == 0 && (long long)p.B * p.L > (2 << 20) && p.rows > 256;
+  // fits, still 498 / 506).  And not in a deterministic layer: which workgroup has a row depends on the batch, and a
+  // token's sums there add in one order whatever the rest of the batch.
+  const bool in_step = p.deterministic || (STAGE == 0 && (long long)p.B * p.L > (2 << 20) && p.rows > 256);
   const int first_slab = in_step ? 0 : int(blockIdx.x % 8) * slabs / 8;
   int slab = first_slab, slot = 0, asked = 0;
   uint32_t had_first = 0, had_second = 0, had_some = 0;
@@ -310,7 +311,7 @@ __device__ __forceinline__ void dense_store(const DenseParams& p, const char* pa
       for (int i = 0; i < 4; ++i) {
         if (c * 16 + i < left) {
           const int t = tok[i] < 0 ? 0 : (tok[i] >= p.B ? p.B - 1 : tok[i]);
-          const int orow = p.per_pair ? j.pair0 + first + c * 16 + i : t;
+          const int orow = p.deterministic ? j.pair0 + first + c * 16 + i : t;
           const float gw = gws[i];
           float* const o = p.out + (size_t)orow * rows + row;
           unsafeAtomicAdd(o, gw * acc[c][0][i]);
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kDenseThreads) void expert_dense_kernel(DenseParams
 // One expert stage (0 gate/up, 1 down) on the matrix cores; hipErrorNotSupported for storage types
 // and shapes it is not built for (bf16; rows a multiple of a granule, inner dimension of a slab).
 hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, const void* wb, void* h_out, float* out,
-                                  int B, int d, int N, int I, int k, oea_dtype dt, Grouping g, bool per_pair,
+                                  int B, int d, int N, int I, int k, oea_dtype dt, Grouping g, bool deterministic,
                                   hipStream_t s) {
   static_assert(kDenseSlab == 64, "dense_stage_fits");
   if (!dense_stage_fits(stage, d, N, I, dt)) return hipErrorNotSupported;
@@ -455,7 +456,7 @@ hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, co
   p.N = N;
   p.B = B;
   p.pairs_max = B * k;
-  p.per_pair = per_pair ? 1 : 0;
+  p.deterministic = deterministic ? 1 : 0;
   for (int c = 2; c <= kMulWaves; ++c)
     if (rows / (stage == 0 ? 16 : 32) % c == 0) p.divisors |= 1 << c;
   static PerDevice attr0, attr1;

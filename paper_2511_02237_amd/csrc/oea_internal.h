@@ -113,10 +113,11 @@ hipError_t launch_route(const float* logits, const uint8_t* token_mask, int L, i
 // the same with a lane per token, for launches of many positions; hipErrorNotSupported otherwise
 hipError_t try_launch_route_lanes(const float* logits, const uint8_t* token_mask, int L, int B, int N, int k, int k0,
                                   RouteOut o, hipStream_t s);
+// deterministic: which kernels route is a matter of B = 128, the line of the deterministic layers' other kernels
 hipError_t launch_router_and_route(const void* x, const void* w_router, const float* bias,
                                    const uint8_t* token_mask, int B, int d, int N, int k, int k0,
                                    oea_dtype dt, float* logits, float* to_zero, size_t n_zero, uint32_t* counter,
-                                   RouteOut o, const RouteGeneralArgs* general, hipStream_t s);
+                                   RouteOut o, const RouteGeneralArgs* general, bool deterministic, hipStream_t s);
 hipError_t launch_route_general(const float* logits, const uint8_t* token_mask, int B, int N, int k0,
                                 const RouteGeneralArgs& ga, int32_t* n_base, RouteOut o, hipStream_t s);
 // most experts a workgroup's rows may belong to
@@ -203,10 +204,11 @@ inline bool dense_stage_fits(int stage, int d, int N, int I, oea_dtype dt) {
   return dt == OEA_BF16 && N <= OEA_MAX_N && rows % (stage == 0 ? 16 : 32) == 0 && L % 64 == 0;
 }
 
-// one expert stage (0 gate/up, 1 down) on the matrix cores, for batches in which experts serve many tokens
+// one expert stage (0 gate/up, 1 down) on the matrix cores, for batches in which experts serve many tokens;
+// deterministic: a row of `out` per pair (down stage), and a token's sums in one order in every batch
 hipError_t try_launch_dense_stage(int stage, const void* vec, const void* wa, const void* wb, void* h_out,
                                   float* out, int B, int d, int N, int I, int k, oea_dtype dt, Grouping g,
-                                  bool per_pair, hipStream_t s);
+                                  bool deterministic, hipStream_t s);
 
 hipError_t launch_read_probe(const void* buf, size_t bytes, uint32_t* sink, hipStream_t s);
 size_t route_lds_bytes(int B, int N);

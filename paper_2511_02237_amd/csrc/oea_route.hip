@@ -9,7 +9,9 @@ namespace {
 constexpr int kRouteThreads = 1024;
 // Larger batches route over many workgroups (see wide_logits_kernel): layer, us, one workgroup / many, d=2048, N=128:
 // B=64 187 / 190, B=96 211 / 210, B=112 215 / 210, B=128 227 / 221; d=512, N=64: B=64 35 / 41.
-constexpr int kWideFromBatch = 96;
+// The two add a token's softmax sum in different orders.  Deterministic layers up to B = 128 give a token the same bits
+// in every batch, so they cross over at the batch where their expert kernels change too.
+constexpr int kWideFromBatch = 96, kWideFromBatchDeterministic = 128;
 
 // One workgroup routes one decode position (blockIdx.x): its B rows of logits and its own output slices.
 // Positions are independent (Section 4: every position and layer is routed separately), so a grid
@@ -161,7 +163,7 @@ __global__ __launch_bounds__(kRouteThreads) void router_route_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batches above 96 tokens: router and routing over many workgroups, as four kernels in stream
+// Batches above 96 tokens (128 with the deterministic combine): router and routing over many workgroups, as four kernels in stream
 // order (a kernel boundary is the grid-wide synchronisation Algorithm 1 needs twice: the union of
 // Phase 1 before Phase 2, all pair counts before the grouped lists).  The union and the counts live
 // in control words of the workspace that the first kernel clears.  With one workgroup per expert
@@ -528,11 +530,11 @@ hipError_t launch_route(const float* logits, const uint8_t* token_mask, int L, i
 template <typename WT>
 static hipError_t launch_rr(const void* x, const void* w_router, const float* bias, const uint8_t* token_mask,
                             int B, int d, int N, int k, int k0, float* logits, float* out_to_zero, size_t n_zero,
-                            uint32_t* counter, RouteOut o, const RouteGeneralArgs* ga, hipStream_t s) {
+                            uint32_t* counter, RouteOut o, const RouteGeneralArgs* ga, bool deterministic, hipStream_t s) {
   RouteGeneral g{1.0, k, N, nullptr};
   const int general = ga && (ga->p < 1.0 || ga->max_p < N) ? 1 : 0;
   if (general) g = RouteGeneral{ga->p, k, ga->max_p, nullptr};
-  if (B > kWideFromBatch && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
+  if (B > (deterministic ? kWideFromBatchDeterministic : kWideFromBatch) && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
     // large batch: router and routing over many workgroups, four kernels in stream order
     const int per_wg = kWideThreads / 64;  // a wavefront per token; small workgroups spread them over the compute units
     hipLaunchKernelGGL((wide_logits_kernel<WT>), dim3((B + 15) / 16, (N + 15) / 16), dim3(64 * kLogitWaves), 0, s,
@@ -588,10 +590,12 @@ static hipError_t launch_rr(const void* x, const void* w_router, const float* bi
 hipError_t launch_router_and_route(const void* x, const void* w_router, const float* bias,
                                    const uint8_t* token_mask, int B, int d, int N, int k, int k0,
                                    oea_dtype dt, float* logits, float* to_zero, size_t n_zero, uint32_t* counter,
-                                   RouteOut o, const RouteGeneralArgs* ga, hipStream_t s) {
+                                   RouteOut o, const RouteGeneralArgs* ga, bool deterministic, hipStream_t s) {
   if (dt == OEA_F32)
-    return launch_rr<float>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga, s);
-  return launch_rr<uint16_t>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga, s);
+    return launch_rr<float>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga,
+                            deterministic, s);
+  return launch_rr<uint16_t>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga,
+                             deterministic, s);
 }
 
 hipError_t launch_route_general(const float* logits, const uint8_t* token_mask, int B, int N, int k0,

@@ -1154,6 +1154,47 @@ def test_deterministic_bits_of_the_single_kernel(torch, B_, B, crowded):
     B_.workspace_check(ws)
 
 
+@pytest.mark.parametrize("case", [
+    # three-kernel layers up to B = 128 (dot-product kernels, on both sides of the batches and pairs at which layers with
+    # the atomic combine change their routing and expert kernels) ...
+    (512, 64, 192, 8, "bf16", (16, 40, 96, 97), 128), (4096, 128, 192, 8, "bf16", (16, 64, 100), 128),
+    (64, 16, 64, 4, "bf16", (20, 96), 120), (448, 24, 160, 8, "f32", (16, 90, 110), 128),
+    # ... and layers above it (matrix cores)
+    (1088, 64, 320, 6, "bf16", (130, 257), 400), (2048, 128, 768, 8, "bf16", (130, 200), 520),
+    (4096, 128, 1536, 8, "bf16", (129, 400), 600)], ids=lambda c: "d%d-N%d-I%d-k%d-%s-B%d" % (c[:5] + c[6:]))
+def test_deterministic_bits_do_not_depend_on_the_batch(torch, B_, case):
+    """oea_decode_ex.deterministic on either side of B = 128: a token's row has the same bits whatever other tokens share
+    the batch, in a batch of few active experts, with others that activate all, or beside padding (k0 = k, so its
+    weights do not depend on the others either)."""
+    d, N, I, k, dtype, sizes, B = case
+    st = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + N)
+    x = torch.empty((B, d), device="cuda").normal_(generator=gen).to(st)
+    x[:sizes[0]] = x[torch.arange(sizes[0], device="cuda") % 2]  # two distinct tokens: at most 2 k active experts
+    w = [torch.empty(s, device="cuda").normal_(0.0, std, generator=gen).to(st)
+         for s, std in (((N, d), d ** -0.5), ((N, I, d), 0.02), ((N, I, d), 0.02), ((N, d, I), 0.02))]
+
+    def layer(rows, mask=None):
+        ws = B_.new_workspace(rows.shape[0], d, N, I, k, deterministic=True)
+        out, tap = B_.moe_decode(rows.contiguous(), *w, k, k, ws, deterministic=True, taps=True, token_mask=mask)
+        return out, tap["gate_w"], int(tap["n_active"][0])
+
+    whole, weights, active = layer(x)
+    seen = set()
+    for n in sizes:
+        out, gw, T = layer(x[:n])
+        seen.add(T)
+        assert torch.equal(gw, weights[:n]), "weights of %d tokens" % n
+        assert torch.equal(out, whole[:n]), "rows of %d tokens" % n
+    mask = torch.zeros(B, dtype=torch.uint8, device="cuda")
+    mask[:sizes[0]] = 1
+    out, gw, T = layer(x, mask)
+    assert T <= 2 * k and (T < active or active == N <= 2 * k)
+    assert torch.equal(gw[:sizes[0]], weights[:sizes[0]]) and torch.equal(out[:sizes[0]], whole[:sizes[0]])
+    assert min(seen) == T
+
+
 def test_cooperative_launch_option(torch, B_, oracle):
     """oea_decode_ex.cooperative: the single kernel through a cooperative launch (co-residency is then
     the runtime's guarantee); same results."""
