@@ -63,10 +63,13 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 //                  d=2048, I=1024, N=160, k0=1 1.8 85 / 82 (B=32), 2.4 145 / 148, 2.9 213 / 210
 static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool masked, bool deterministic) {
   if (deterministic) return B > 128;
+  // How many tokens of a masked batch are padding is not known here, and with few live ones the other kernels lead:
+  // B=128, k0=3, d=4096, I=1536 16 live 267 / 287, 64 652 / 633, 128 1060 / 764; B=64, k0=3, d=4096, I=192 4 live 45 / 55, 16
+  // 65 / 68, 64 124 / 108; B=32, k0=1 8 live 38 / 47.  So masked layers leave them only above the single kernel's batches.
+  if (masked) return B > 128 && d % 256 == 0 && I % 128 == 0;
   if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
   const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
-  double pairs = double(B) * (k < active ? k : active) / active;  // a token has at most the active ones
-  if (masked) pairs *= 0.7;  // some of the tokens are padding (B=126, 72 live, d=2048, I=768, k0=8: 212 / 222)
+  const double pairs = double(B) * (k < active ? k : active) / active;  // a token has at most the active ones
   if (!fused_kernel_shape(d, I)) {
     // few experts with long rows: a workgroup's walk over the slabs (about 0.45 us each) outlasts what the other kernels
     // need for the weights (5.5 TB/s) and the pairs (d=4096, I=192, k0=2: B=8 42 / 48, B=12 48 / 55; d=1024, I=256,

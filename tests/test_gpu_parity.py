@@ -203,10 +203,10 @@ def experts_in_a_share(expert_idx, rows, beta, n_wg):
     return int((last // rows - first[:-1] // rows + 1)[last >= first[:-1]].max())
 
 
-def expert_kernels(torch, B_, dev, k, k0, ws, path, deterministic):
+def expert_kernels(torch, B_, dev, k, k0, ws, path, deterministic, token_mask=None, top_p=None, max_p=None):
     """The kernels that a call's two expert stages run on (oea_test_opts.h_kernels)."""
     args, _, shape = B_._layer_args(*(dev[f] for f in ("x", "w_router", "w_gate", "w_up", "w_down")), k, k0, None)
-    ex, _ = B_._extras(shape, k, "cuda", None, None, False, None, None, deterministic=deterministic)
+    ex, _ = B_._extras(shape, k, "cuda", None, token_mask, False, top_p, max_p, deterministic=deterministic)
     kernels = (ctypes.c_int32 * 2)(-1, -1)
     opts = B_.test_opts(kernel_path=path, kernels=kernels)
     B_._check(B_.lib().moe_decode_test(*args, B_._ptr(ws), ws.numel(), B_._stream(None),
@@ -258,6 +258,42 @@ def test_kernels_chosen_per_stage(torch, B_, oracle, shape):
     assert expert_kernels(torch, B_, dev, k, k0, B_.new_workspace(B, d, N, I, k), None, False) == kernels
     out, tap = run_layer_dev(torch, B_, L, dev, k0)
     check_layer(oracle, L, k0, out, tap, str(shape))
+
+
+SHARE = (4096, 128, 192, 8)  # the 235B layer's share of one of eight GPUs
+D30, D235 = (2048, 128, 768, 8), (4096, 128, 1536, 8)
+
+
+@pytest.mark.parametrize("layer,B,k0,opts,kernels", [
+    # matrix cores where an active expert serves enough pairs, and above the single kernel's batches
+    (SHARE, 64, 3, {}, "matrix"), (SHARE, 8, 3, {}, "dot"), (SHARE, 200, 3, {}, "matrix"), ((512, 60, 512, 8), 32, 3, {}, "matrix"),
+    ((512, 60, 512, 8), 4, 1, {}, "dot"), (D30, 16, 3, {}, "single"), (D30, 128, 3, {}, "single"), (D30, 96, 1, {}, "matrix"),
+    (D30, 129, 3, {}, "matrix"), (D235, 16, 5, {}, "single"), (D235, 96, 3, {}, "matrix"),
+    # with the deterministic combine above B = 128 alone
+    (D235, 128, 3, dict(deterministic=True), "single"), (D235, 129, 3, dict(deterministic=True), "matrix"),
+    (SHARE, 128, 3, dict(deterministic=True), "dot"), (SHARE, 129, 3, dict(deterministic=True), "matrix"),
+    # with a padding mask the live tokens may be few: matrix cores above the single kernel's batches only
+    (SHARE, 64, 3, dict(live=4), "dot"), (SHARE, 64, 3, dict(live=64), "dot"), (SHARE, 200, 3, dict(live=8), "dot"),
+    (D235, 128, 3, dict(live=16), "single"), (D235, 48, 1, dict(live=4), "single"), (D235, 129, 3, dict(live=129), "matrix"),
+    ((512, 60, 512, 8), 32, 3, dict(live=3), "dot"), ((4096, 128, 384, 8), 129, 3, dict(live=129), "matrix"),
+], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else "-".join("%s=%s" % i for i in v.items()) if isinstance(v, dict) else str(v))
+def test_kernels_chosen_automatically(torch, B_, layer, B, k0, opts, kernels):
+    """The automatic choice between the single kernel, the dot-product kernels and the matrix cores, on both sides of its
+    lines, for the forms that a call can have."""
+    d, N, I, k = layer
+    opts = dict(opts)
+    live = opts.pop("live", None)
+    if live is not None:
+        opts["token_mask"] = (torch.arange(B, device="cuda") < live).to(torch.uint8)
+    det = opts.pop("deterministic", False)
+    dev = {f: torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+           for f, s in (("x", (B, d)), ("w_router", (N, d)), ("w_gate", (N, I, d)), ("w_up", (N, I, d)), ("w_down", (N, d, I)))}
+    ws = B_.new_workspace(B, d, N, I, k, deterministic=det)
+    got = expert_kernels(torch, B_, dev, k, k0, ws, None, det, **opts)
+    if kernels == "dot":
+        assert set(got) <= {1, 3}, got
+    else:
+        assert got == {"single": [0, 0], "matrix": [4, 4]}[kernels], got
 
 
 @pytest.mark.parametrize("shape", [(129, 8, 3, "bf16"), (144, 32, 16, "bf16"), (145, 264, 17, "f32"), (160, 1032, 130, "bf16"),
