@@ -46,11 +46,10 @@ static int check_route_sizes(int B, int N, int k, int k0) {
   return OEA_OK;
 }
 
-// Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
-// batches at the sizes that it is built for, else where an active expert serves enough pairs.  The number of active
-// experts is the one that B independent choices of k0 among N give (a batch of similar tokens has fewer, and more pairs
-// on each).  With the deterministic combine the line is B = 128 alone: below it the kernels give a token the same bits in
-// every batch (above a handful of tokens, where small stages change kernels), above it the matrix cores do.
+// Whether an active expert is expected to serve enough pairs for the matrix cores, every token selecting a baseline of
+// k0 and up to k experts in all.  The number of active experts is the one that B independent choices of k0 among N give (a
+// batch of similar tokens has fewer, and more pairs on each), and of a token's ranks behind the baseline up to max_p as
+// large a part is active as of all experts.
 // Measured with token batches that change from call to call, us, other kernels / matrix cores:
 //   single kernel, d=2048, I=768, N=128, k=8   k0=3: 5.1 pairs 177 / 187 (B=64), 5.9 198 / 197, 6.7 213 / 211,
 //                                               7.5 234 / 215, 8.4 240 / 227 (B=128); k0=1: 11.4 167 / 144; k0=8: 6.0 232 / 237
@@ -61,15 +60,12 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 //                  d=512, I=512, N=60, k0=3    3.2 31 / 27 (B=9), 5.6 46 / 33;  d=512, I=192, N=64  3.1 29 / 26 (B=32), 8.3 48 / 34
 //                  d=1024, I=256, N=24         4.9 29 / 27 (B=9), 12 40 / 30;   d=64, I=64, N=16    3.2 23 / 22 (B=9), 17 40 / 24
 //                  d=2048, I=1024, N=160, k0=1 1.8 85 / 82 (B=32), 2.4 145 / 148, 2.9 213 / 210
-static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool masked, bool deterministic) {
-  if (deterministic) return B > 128;
-  // How many tokens of a masked batch are padding is not known here, and with few live ones the other kernels lead:
-  // B=128, k0=3, d=4096, I=1536 16 live 267 / 287, 64 652 / 633, 128 1060 / 764; B=64, k0=3, d=4096, I=192 4 live 45 / 55, 16
-  // 65 / 68, 64 124 / 108; B=32, k0=1 8 live 38 / 47.  So masked layers leave them only above the single kernel's batches.
-  if (masked) return B > 128 && d % 256 == 0 && I % 128 == 0;
-  if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
+//   max_p, k0=3    d=4096, I=1536 3 of 128 1.9 582 / 622 (B=64), 8 4.4 623 / 646;  d=4096, I=192 3 of 128 1.4 79 / 82 (B=32), 2.6 125 /
+//                  126 (B=100), 8 6.5 154 / 127
+static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, int max_p) {
   const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
-  const double pairs = double(B) * (k < active ? k : active) / active;  // a token has at most the active ones
+  const double selects = max_p > k0 ? k0 + (max_p - k0) * (active - k0) / (N - k0) : k0;
+  const double pairs = double(B) * (k < selects ? k : selects) / active;
   if (!fused_kernel_shape(d, I)) {
     // few experts with long rows: a workgroup's walk over the slabs (about 0.45 us each) outlasts what the other kernels
     // need for the weights (5.5 TB/s) and the pairs (d=4096, I=192, k0=2: B=8 42 / 48, B=12 48 / 55; d=1024, I=256,
@@ -79,6 +75,23 @@ static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, bool 
   }
   // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
   return d == 4096 ? B >= 48 && pairs >= 5.0 : B > 64 && pairs >= 9.0;
+}
+
+// Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
+// batches at the sizes that it is built for, else where an active expert serves enough pairs.
+// With the deterministic combine the line is B = 128 alone: below it the kernels give a token the same bits in
+// every batch (above a handful of tokens, where small stages change kernels), above it the matrix cores do.
+static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, const RouteGeneralArgs& ga, bool masked,
+                                bool deterministic) {
+  if (deterministic) return B > 128;
+  // How many tokens of a masked batch are padding is not known here, and with few live ones the other kernels lead:
+  // B=128, k0=3, d=4096, I=1536 16 live 267 / 287, 64 652 / 633, 128 1060 / 764; B=64, k0=3, d=4096, I=192 4 live 45 / 55, 16
+  // 65 / 68, 64 124 / 108; B=32, k0=1 8 live 38 / 47.  So masked layers leave them only above the single kernel's batches.
+  if (masked) return B > 128 && d % 256 == 0 && I % 128 == 0;
+  if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
+  // a top-p cut leaves a baseline of one to k0 experts: worth it at both ends
+  return pairs_for_matrix_cores(B, d, N, I, k, k0, ga.max_p) &&
+         (ga.p >= 1.0 || k0 == 1 || pairs_for_matrix_cores(B, d, N, I, k, 1, ga.max_p));
 }
 
 // Stages with little work per wavefront keep the streaming kernels with fixed shares: the stage kernels' share by
@@ -291,7 +304,8 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   hipError_t e = hipErrorNotSupported;
   // (above B = 128 a stage that fits runs on the matrix cores even if the other does not)
   const bool dense_fits = dense_stage_fits(0, d, N, I, dt) && dense_stage_fits(1, d, N, I, dt);
-  const bool dense = path == 4 || (path == 0 && (dense_fits || B > 128) && prefer_matrix_cores(B, d, N, I, k, k0, ex && ex->token_mask, y != nullptr));
+  const bool dense = path == 4 || (path == 0 && (dense_fits || B > 128) &&
+                                   prefer_matrix_cores(B, d, N, I, k, k0, ga, ex && ex->token_mask, y != nullptr));
   if (path == 0 && !dense)
     e = try_launch_fused(x, W_router, W_gate, W_up, W_down, ex ? ex->router_bias : nullptr,
                          ex ? ex->token_mask : nullptr, out, logits, h, ro,

@@ -276,6 +276,13 @@ D30, D235 = (2048, 128, 768, 8), (4096, 128, 1536, 8)
     (SHARE, 64, 3, dict(live=4), "dot"), (SHARE, 64, 3, dict(live=64), "dot"), (SHARE, 200, 3, dict(live=8), "dot"),
     (D235, 128, 3, dict(live=16), "single"), (D235, 48, 1, dict(live=4), "single"), (D235, 129, 3, dict(live=129), "matrix"),
     ((512, 60, 512, 8), 32, 3, dict(live=3), "dot"), ((4096, 128, 384, 8), 129, 3, dict(live=129), "matrix"),
+    # a narrow rank window leaves few pairs to an expert, a wide one does not
+    (D235, 128, 3, dict(max_p=3), "single"), (D235, 128, 3, dict(max_p=24), "matrix"), (D235, 64, 1, dict(max_p=2), "single"),
+    (D30, 128, 1, dict(max_p=2), "single"), (SHARE, 100, 3, dict(max_p=3), "dot"), (SHARE, 100, 3, dict(max_p=8), "matrix"),
+    ((64, 16, 64, 16), 20, 16, dict(max_p=8), "matrix"),
+    # a top-p cut leaves a baseline of one to k0 experts
+    (SHARE, 48, 5, dict(top_p=0.1), "matrix"), (SHARE, 14, 8, dict(top_p=0.1), "dot"), (SHARE, 48, 5, dict(top_p=0.1, max_p=6), "dot"),
+    ((512, 60, 512, 8), 32, 3, dict(top_p=0.1), "matrix"),
 ], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else "-".join("%s=%s" % i for i in v.items()) if isinstance(v, dict) else str(v))
 def test_kernels_chosen_automatically(torch, B_, layer, B, k0, opts, kernels):
     """The automatic choice between the single kernel, the dot-product kernels and the matrix cores, on both sides of its
