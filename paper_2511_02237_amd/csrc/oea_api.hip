@@ -78,7 +78,8 @@ static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, in
 }
 
 // Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
-// batches at the sizes that it is built for, else where an active expert serves enough pairs.
+// batches with d a multiple of 256 and I of 128 (B=130, k=k0=1, 1.1 pairs, d=2048, I=384, N=512 141 / 122; d=4096, N=128 I=384,
+// 1.6 pairs 153 / 159, I=640 238 / 243), else where an active expert serves enough pairs.
 // With the deterministic combine the line is B = 128 alone: below it the kernels give a token the same bits in
 // every batch (above a handful of tokens, where small stages change kernels), above it the matrix cores do.
 static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, const RouteGeneralArgs& ga, bool masked,
@@ -87,8 +88,8 @@ static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, const
   // How many tokens of a masked batch are padding is not known here, and with few live ones the other kernels lead:
   // B=128, k0=3, d=4096, I=1536 16 live 267 / 287, 64 652 / 633, 128 1060 / 764; B=64, k0=3, d=4096, I=192 4 live 45 / 55, 16
   // 65 / 68, 64 124 / 108; B=32, k0=1 8 live 38 / 47.  So masked layers leave them only above the single kernel's batches.
-  if (masked) return B > 128 && d % 256 == 0 && I % 128 == 0;
-  if (B > 128 && d % 256 == 0 && I % 256 == 0) return true;
+  const bool always = B > 128 && d % 256 == 0 && I % 128 == 0;
+  if (masked || always) return always;
   // a top-p cut leaves a baseline of one to k0 experts: worth it at both ends
   return pairs_for_matrix_cores(B, d, N, I, k, k0, ga.max_p) &&
          (ga.p >= 1.0 || k0 == 1 || pairs_for_matrix_cores(B, d, N, I, k, 1, ga.max_p));

@@ -269,6 +269,8 @@ D30, D235 = (2048, 128, 768, 8), (4096, 128, 1536, 8)
     (SHARE, 64, 3, {}, "matrix"), (SHARE, 8, 3, {}, "dot"), (SHARE, 200, 3, {}, "matrix"), ((512, 60, 512, 8), 32, 3, {}, "matrix"),
     ((512, 60, 512, 8), 4, 1, {}, "dot"), (D30, 16, 3, {}, "single"), (D30, 128, 3, {}, "single"), (D30, 96, 1, {}, "matrix"),
     (D30, 129, 3, {}, "matrix"), (D235, 16, 5, {}, "single"), (D235, 96, 3, {}, "matrix"),
+    # (in multiples of 256 and 128 always above them, also with about one pair to an expert)
+    ((2048, 512, 384, 1), 130, 1, {}, "matrix"), ((2048, 512, 384, 1), 128, 1, {}, "dot"), ((2048, 512, 320, 1), 130, 1, {}, "dot"),
     # with the deterministic combine above B = 128 alone
     (D235, 128, 3, dict(deterministic=True), "single"), (D235, 129, 3, dict(deterministic=True), "matrix"),
     (SHARE, 128, 3, dict(deterministic=True), "dot"), (SHARE, 129, 3, dict(deterministic=True), "matrix"),
