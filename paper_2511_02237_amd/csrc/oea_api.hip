@@ -66,12 +66,16 @@ static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, in
   const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
   const double selects = max_p > k0 ? k0 + (max_p - k0) * (active - k0) / (N - k0) : k0;
   const double pairs = double(B) * (k < selects ? k : selects) / active;
-  if (!fused_kernel_shape(d, I)) {
+  if (!fused_kernel_takes(B, d, N, I, k, OEA_BF16)) {
     // few experts with long rows: a workgroup's walk over the slabs (about 0.45 us each) outlasts what the other kernels
     // need for the weights (5.5 TB/s) and the pairs (d=4096, I=192, k0=2: B=8 42 / 48, B=12 48 / 55; d=1024, I=256,
     // k0=1: B=4 24 / 27, B=12 31 / 28; d=2048, I=1024, k0=1: B=6 43 / 45, B=8 50 / 45)
     const double walk = 0.45 * (d + I) / 64, other = active * 6.0 * d * I / 5.5e6 + 1.2 * pairs;
-    return B > 4 && pairs >= 3.2 && walk <= other;
+    // (the single kernel's layers with more experts or more experts per token than it takes: d=2048, I=768, N=160 4.6 217 / 226
+    // and 221 / 211 (B=64), 5.2 239 / 244, 6.7 284 / 259; d=4096, I=1536, N=160 4.7 729 / 699; k=20 5.0 53 / 47, 9.6 158 / 140 and
+    // 573 / 438)
+    const double line = fused_kernel_shape(d, I) ? 5.5 : 3.2;
+    return B > 4 && pairs >= line && walk <= other;
   }
   // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
   return d == 4096 ? B >= 48 && pairs >= 5.0 : B > 64 && pairs >= 9.0;

@@ -1296,8 +1296,7 @@ hipError_t try_launch_fused(const void* x, const void* w_router, const void* w_g
                             float* logits, void* h, RouteOut ro, uint32_t* ctrl, int B, int d, int N, int I,
                             int k, int k0, oea_dtype dt, hipStream_t s, uint32_t spin_limit, bool cooperative,
                             float* y_per_pair, const RouteGeneralArgs* general) {
-  if (dt != OEA_BF16 || N > 128 || B > 128 || k > 16) return hipErrorNotSupported;
-  if (!fused_kernel_shape(d, I)) return hipErrorNotSupported;
+  if (!fused_kernel_takes(B, d, N, I, k, dt)) return hipErrorNotSupported;
   const bool shape30 = d == 2048;
   int dev = 0, grid = 0;
   if (!current_device(&dev, &grid)) return hipErrorUnknown;

@@ -198,6 +198,10 @@ hipError_t try_launch_stage_kernels(int stage, const void* vec, const void* wa, 
 
 // the layer shapes that the single kernel is built for
 inline bool fused_kernel_shape(int d, int I) { return (d == 2048 && I == 768) || (d == 4096 && I == 1536); }
+// ... and the layers that it takes if their vectors fit LDS
+inline bool fused_kernel_takes(int B, int d, int N, int I, int k, oea_dtype dt) {
+  return dt == OEA_BF16 && N <= 128 && B <= 128 && k <= 16 && fused_kernel_shape(d, I);
+}
 // the stages that the matrix-core kernel is built for: whole granules of rows, whole slabs of the inner dimension
 inline bool dense_stage_fits(int stage, int d, int N, int I, oea_dtype dt) {
   const int rows = stage == 0 ? I : d, L = stage == 0 ? d : I;

@@ -271,6 +271,9 @@ D30, D235 = (2048, 128, 768, 8), (4096, 128, 1536, 8)
     (D30, 129, 3, {}, "matrix"), (D235, 16, 5, {}, "single"), (D235, 96, 3, {}, "matrix"),
     # (in multiples of 256 and 128 always above them, also with about one pair to an expert)
     ((2048, 512, 384, 1), 130, 1, {}, "matrix"), ((2048, 512, 384, 1), 128, 1, {}, "dot"), ((2048, 512, 320, 1), 130, 1, {}, "dot"),
+    # the single kernel's d and I with more experts, or more of them per token, than it takes
+    ((2048, 160, 768, 8), 64, 3, {}, "dot"), ((2048, 160, 768, 8), 128, 3, {}, "matrix"), ((2048, 128, 768, 20), 32, 3, {}, "matrix"),
+    ((4096, 128, 1536, 20), 32, 3, {}, "matrix"), ((4096, 128, 1536, 16), 64, 8, {}, "matrix"),
     # with the deterministic combine above B = 128 alone
     (D235, 128, 3, dict(deterministic=True), "single"), (D235, 129, 3, dict(deterministic=True), "matrix"),
     (SHARE, 128, 3, dict(deterministic=True), "dot"), (SHARE, 129, 3, dict(deterministic=True), "matrix"),
