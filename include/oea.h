@@ -157,8 +157,8 @@ int oea_route_general(const float *router_logits, const uint8_t *token_mask, int
  * the call gives up, its output is undefined and oea_workspace_check reports OEA_ERR_TIMEOUT).
  * A caller that runs other kernels beside the layer (a second stream) sets
  * oea_decode_ex.cooperative, which makes co-residency the runtime's guarantee.  Still larger batches, and
- * smaller ones in which an active expert can be expected to serve many tokens (at these two shapes five to nine,
- * elsewhere three; never with oea_decode_ex.deterministic), run as separate kernels (router + routing, gate/up stage,
+ * smaller ones in which an active expert can be expected to serve many tokens (at these two shapes six to nine, elsewhere
+ * three to six; never with oea_decode_ex.deterministic or token_mask), run as separate kernels (router + routing, gate/up stage,
  * down stage) with the expert stages on the matrix cores (bf16, d and I multiples of 64: the arithmetic per pair,
  * Eq. 2's second term, would bound the vector ALUs); every other shape, and fp32
  * storage, runs as three kernels with dot-product expert kernels (which of them depends on the sizes).

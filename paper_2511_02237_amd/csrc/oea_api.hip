@@ -54,7 +54,9 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 //   single kernel, d=2048, I=768, N=128, k=8   k0=3: 5.1 pairs 177 / 187 (B=64), 5.9 198 / 197, 6.7 213 / 211,
 //                                               7.5 234 / 215, 8.4 240 / 227 (B=128); k0=1: 11.4 167 / 144; k0=8: 6.0 232 / 237
 //   single kernel, d=4096, I=1536, N=128, k=8  k0=3: 3.9 435 / 440 (B=32), 4.4 556 / 552, 5.1 646 / 631, 5.9 712 / 683,
-//                                               8.4 1102 / 789 (B=128); k0=1: 10 440 / 345; k0=8: 4.1 784 / 783
+//                                               8.4 1102 / 789 (B=128); k0=1: 10 440 / 345; k0=8: 4.1 784 / 783, 5.0 787 / 828
+//                                               and 784 / 834 (B=80), 6.0 928 / 778 and 840 / 783; again on other boxes: k0=3: 5.1
+//                                               646 / 627 and 611 / 609, 5.9 708 / 683 and 719 / 665; k0=2: 5.5 436 / 443 and 437 / 447
 //   dot-product kernels (the better of streaming and stage kernels)
 //                  d=4096, I=192, N=128, k0=3  3.0 56 / 60 (B=16), 3.4 72 / 70, 4.4 107 / 101, 5.1 125 / 109, 8.5 187 / 133 (B=130)
 //                  d=512, I=512, N=60, k0=3    3.2 31 / 27 (B=9), 5.6 46 / 33;  d=512, I=192, N=64  3.1 29 / 26 (B=32), 8.3 48 / 34
@@ -74,11 +76,15 @@ static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, in
     // (the single kernel's layers with more experts or more experts per token than it takes: d=2048, I=768, N=160 4.6 217 / 226
     // and 221 / 211 (B=64), 5.2 239 / 244, 6.7 284 / 259; d=4096, I=1536, N=160 4.7 729 / 699; k=20 5.0 53 / 47, 9.6 158 / 140 and
     // 573 / 438)
-    const double line = fused_kernel_shape(d, I) ? 5.5 : 3.2;
+    // Experts of 12 MB and more stream for so long that the pairs are hidden for longer, on rows of up to 4096 (k0=3, d=4096, I=1024,
+    // N=128 3.3 212 / 212 and 209 / 220 (B=20), 3.9 289 / 298 and 300 / 312, 4.5 372 / 366 and 346 / 348, 5.1 448 / 421; d=2048,
+    // I=1024 3.9 163 / 167, 4.4 200 / 191 and 200 / 203, 5.1 233 / 225; d=2048, I=1408, N=64, k=6 3.4 139 / 146 and 140 / 138, 4.7
+    // 174 / 176 and 176 / 166; longer rows, d=5120, I=1536, N=160, k=6 3.7 1161 / 818).
+    const double line = fused_kernel_shape(d, I) ? 5.5 : d <= 4096 && d * I >= (2 << 20) ? 4.4 : 3.2;
     return B > 4 && pairs >= line && walk <= other;
   }
   // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
-  return d == 4096 ? B >= 48 && pairs >= 5.0 : B > 64 && pairs >= 9.0;
+  return d == 4096 ? B >= 48 && pairs >= 5.9 : B > 64 && pairs >= 9.0;
 }
 
 // Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
