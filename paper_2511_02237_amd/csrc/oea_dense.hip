@@ -205,11 +205,13 @@ __device__ __forceinline__ void dense_load_wave(const DenseParams& p, const Dens
   // The chip's eight XCDs walk the columns from eight different ones on: all workgroups at one column offset of rows that
   // lie a power of two apart crowd the same memory channels (gate/up, us, from column 0 / like this: d=4096, I=192, B=200
   // 88 / 67, B=1000 93 / 72; I=1536, B=160 543 / 510; d=2048, I=768, B=512 139 / 136, B=1000 161 / 153).  Not where the
-  // token rows of the whole batch do not fit an XCD's L2 and many jobs read them: in step the XCDs find in the
+  // token rows of the whole batch do not fit an XCD's L2 and an expert's many jobs read them: in step the XCDs find in the
   // memory-side cache what one of them has fetched (d=4096, I=1536: B=600 530 / 543, B=1000 549 / 578; at B=400, which
-  // fits, still 498 / 506).  And not in a deterministic layer: which workgroup has a row depends on the batch, and a
-  // token's sums there add in one order whatever the rest of the batch.
-  const bool in_step = p.deterministic || (STAGE == 0 && (long long)p.B * p.L > (2 << 20) && p.rows > 256);
+  // fits, still 498 / 506).  With fewer jobs the channels count for more (layers, d=4096, B=1000: I=1536 882 / 888, I=768 505 /
+  // 491, I=384 341 / 310, I=192 244 / 233; d=8192, I=512, N=32, B=600 249 / 234; d=3072, I=1024, N=64 424 / 422).  And not in a
+  // deterministic layer: which workgroup has a row depends on the batch, and a token's sums there add in one order
+  // whatever the rest of the batch.
+  const bool in_step = p.deterministic || (STAGE == 0 && (long long)p.B * p.L > (2 << 20) && p.rows > 1024);
   const int first_slab = in_step ? 0 : int(blockIdx.x % 8) * slabs / 8;
   int slab = first_slab, slot = 0, asked = 0;
   uint32_t had_first = 0, had_second = 0, had_some = 0;
