@@ -923,9 +923,10 @@ def test_many_tokens_per_expert(torch, B_, oracle):
 
 
 def test_matrix_core_stages(torch, B_, oracle):
-    """The expert stages on the matrix cores (kernel path 4; the automatic choice above B=128): batches
-    in which an expert serves a few tokens (one partly filled group of 16), many (several groups), and
-    more than one pass holds (over 64); the skewed workload; padding; the deterministic combine."""
+    """The expert stages on the matrix cores (kernel path 4, and the automatic choice, which takes them above B=128 at
+    these sizes): batches in which an expert serves a few tokens (one partly filled group of 16), many (several groups), and
+    more than 64; the skewed workload; padding; the deterministic combine.  (More tokens than the 128 of a pass:
+    test_matrix_core_granules.)"""
     L0 = W.make_layer("qwen3_30b", 2100, B=160)
     dev_w = {f: B_.to_device(getattr(L0, f)) for f in ("w_router", "w_gate", "w_up", "w_down")}
 
@@ -958,13 +959,12 @@ def test_matrix_core_stages(torch, B_, oracle):
         err, ref = check_layer(oracle, Lsk, k0, out, tap, "matrix cores skew k0=%d" % k0, bias=Ls.router_bias)
         say("matrix cores skew k0=%d: T=%d err=%.2e" % (k0, ref["n_active"], err))
     # automatic choice above B=128: three distinct tokens in turn, so experts serve about 85 of the 256
-    # tokens (a pass of 64 and one of the rest); padding mask
+    # tokens (six groups of 16, the last one ragged); padding mask
     x = np.ascontiguousarray(L0.x[np.arange(256) % 3])
     mask = np.ones(256, np.uint8)
     mask[[0, 100, 255]] = 0
     L, dev = case("matrix cores B=256, three distinct tokens, automatic path, mask", x, 3, None, mask=mask, min_pairs=65)
-    # small shapes: both stages on the matrix cores (several experts per workgroup, more workgroups than
-    # units), and one where only the gate/up stage qualifies (I = 128: the down stage keeps the dot products)
+    # small shapes: both stages on the matrix cores (several experts per workgroup, more workgroups than units)
     for (d, I, N, B, k) in [(512, 256, 6, 200, 3), (256, 256, 3, 40, 2), (256, 128, 8, 40, 2), (1024, 512, 20, 300, 4)]:
         Lt = W.make_layer("toy", 640, d=d, I=I, N=N, B=B, k=k, dtype="bf16")
         for k0 in (1, k):
@@ -1210,6 +1210,8 @@ def test_deterministic_bits_of_the_single_kernel(torch, B_, B, crowded):
     # the atomic combine change their routing and expert kernels) ...
     (512, 64, 192, 8, "bf16", (16, 40, 96, 97), 128), (4096, 128, 192, 8, "bf16", (16, 64, 100), 128),
     (64, 16, 64, 4, "bf16", (20, 96), 120), (448, 24, 160, 8, "f32", (16, 90, 110), 128),
+    # the single kernel, and at d=4096 the batches whose vectors do not fit its LDS (18 to 32 tokens)
+    (2048, 128, 768, 8, "bf16", (5, 16, 33, 97), 128), (4096, 128, 1536, 8, "bf16", (9, 17, 24, 33), 100),
     # ... and layers above it (matrix cores)
     (1088, 64, 320, 6, "bf16", (130, 257), 400), (2048, 128, 768, 8, "bf16", (130, 200), 520),
     (4096, 128, 1536, 8, "bf16", (129, 400), 600)], ids=lambda c: "d%d-N%d-I%d-k%d-%s-B%d" % (c[:5] + c[6:]))
@@ -1318,6 +1320,28 @@ def test_matrix_core_granules(torch, B_, oracle, shape):
         check_layer(oracle, L, k0, outs[-1], {n: v.cpu().numpy() for n, v in tap.items()}, str(shape), mask=mask)
     if det:
         assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["atomics", "det"])
+@pytest.mark.parametrize("shape", [
+    # I in whole granules of the gate/up stage and no whole slabs of the down stage, and d the other way round (whole granules of
+    # the down stage, no whole slabs of the gate/up stage); automatic choice above B = 128 and below
+    (40, 512, 6, 80, 3, 2, 4, [4, None]), (200, 512, 6, 80, 3, 2, None, [4, None]), (100, 512, 6, 80, 3, 2, None, [None, None]),
+    (200, 1024, 24, 1040, 4, 2, None, [4, None]), (40, 96, 6, 64, 3, 2, 4, [None, 4]), (200, 96, 6, 128, 3, 2, None, [None, 4])],
+    ids=lambda c: "B%d-d%d-N%d-I%d-k%d-k0%d-path%s" % c[:7])
+def test_one_stage_on_the_matrix_cores(torch, B_, oracle, shape, det):
+    """Layers of which only one stage fits the matrix-core kernel: the other one keeps the dot products, and they hand the
+    hidden vectors over."""
+    B, d, N, I, k, k0, path, stages = shape
+    L = W.make_layer("toy", 3300 + B, d=d, I=I, N=N, B=B, k=k, dtype="bf16")
+    ws = B_.new_workspace(B, d, N, I, k, deterministic=det)
+    dev = {f: B_.to_device(getattr(L, f)) for f in ("x", "w_router", "w_gate", "w_up", "w_down")}
+    got = expert_kernels(torch, B_, dev, k, k0, ws, path, det)
+    assert all(g == 4 if s == 4 else g in (1, 3) for g, s in zip(got, stages)), got
+    out, tap = B_.moe_decode(dev["x"], dev["w_router"], dev["w_gate"], dev["w_up"], dev["w_down"], k, k0, ws, taps=True,
+                             deterministic=det, kernel_path=path)
+    torch.cuda.synchronize()
+    check_layer(oracle, L, k0, out.cpu().numpy(), {n: v.cpu().numpy() for n, v in tap.items()}, str(shape))
 
 
 @pytest.mark.parametrize("det", [False, True], ids=["atomics", "det"])
