@@ -560,9 +560,11 @@ def run(args):
 
     # ---- per-kernel durations with HIP events recorded inside the library around each kernel
     kern = {}
+    stage_kernels = (ctypes.c_int32 * 2)(-1, -1)  # which kernels the library chose (include/oea_testing.h, h_kernels)
     evs = (ctypes.c_void_p * 6)(*[hip.event() for _ in range(6)])
     for k0 in sorted({args.k0, k}):
-        ev_opts = binding.test_opts(kernel_path=args.kernel_path, kernel_events=evs)
+        ev_opts = binding.test_opts(kernel_path=args.kernel_path, kernel_events=evs,
+                                    kernels=stage_kernels if k0 == args.k0 else None)
         calls = [make_call(xs[j % len(xs)], sets[j % R], k0, ev_opts) for j in range(R * len(xs))]  # rotating, as timed
         acc = np.zeros(3)
         n = min(args.steps, 100)
@@ -683,10 +685,10 @@ def run(args):
     else:
         dom_us = kern[args.k0][1]
         dom_bytes = T0 * 2 * d * I * 2 + pairs0 * d * 2 + pairs0 * I * 2  # weights + gathered x + hidden written
-        # which gate/up kernel that is follows the library's choice (see include/oea_testing.h, kernel_path)
-        dom_name = ("expert_dense_kernel<gate/up> (matrix cores)" if (args.kernel_path == 4 or (args.kernel_path == 0 and B > 128))
-                    else "expert_stage_kernel<bf16, gate/up>" if args.kernel_path in (0, 3)
-                    else "expert_stream_kernel<bf16, gate/up>" if args.kernel_path == 2 else "expert_kernel<bf16, gate/up>")
+        dom_name = ("expert_dense_kernel<gate/up> (matrix cores)" if stage_kernels[0] == 4
+                    else "expert_stage_kernel<bf16, gate/up>" if stage_kernels[0] == 3
+                    else "expert_kernel<bf16, gate/up>" if args.kernel_path == 1
+                    else "expert_stream_kernel<bf16, gate/up> (or expert_kernel where the vectors do not fit LDS)")
     achieved = dom_bytes / dom_us / 1e3
     # traffic: HBM bytes per launch from the rocprofv3 --pmc passes over this same command, RECORDED in
     # profiles/ (counters cannot be read from inside the run); quoted only if the kernel sources are the ones

@@ -18,14 +18,17 @@ typedef struct {
   int32_t kernel_path;    /* which expert-FFN kernels this call uses:
                                0 = automatic: the single fused kernel for the shapes and batch sizes
                                    it is built for, else three kernels (router + routing, gate/up,
-                                   down) with the best expert kernels that apply
+                                   down) with the best expert kernels that apply; the matrix cores
+                                   where an expert is expected to serve enough tokens (oea.h, moe_decode)
                                1 = three kernels, generic expert kernels only (any shape, any batch)
                                2 = three kernels, streaming expert kernels with fixed shares when
                                    the token vectors fit in LDS, else generic ones
                                3 = three kernels, the fused kernel's stage code as expert kernels
                                    where the shape allows
                                4 = three kernels, expert stages on the matrix cores where the shape
-                                   allows (bf16; the automatic choice uses them above B = 128) */
+                                   allows (bf16, d and I multiples of 64; a stage whose rows are a multiple
+                                   of 16 (gate/up) or 32 (down) and whose columns are one of 64 runs
+                                   there even if the other stage does not) */
   uint32_t spin_limit;    /* polls after which a wait inside the single kernel gives up (0 = the
                              default, about a second; all of a workgroup's hidden vectors count as
                              one wait, in which a poll takes eight); 1 forces every wait to give up */

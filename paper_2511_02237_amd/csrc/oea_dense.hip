@@ -21,10 +21,12 @@
 //
 // Bound by the weight stream: a loop of these requests alone reaches 7.0 TB/s with two slabs of 32 KB in flight per
 // compute unit (128-byte pieces or whole rows, one barrier per slab or none; 6.2 without the non-temporal hint); the
-// kernel without its results 6.3 to 6.5.  What is left are the results (B=512, d=2048, I=768: gate/up 13 us,
-// down 17 us; B=1000, d=4096, I=1536: 37 and 64 us).  Before, every wavefront loaded into registers, multiplied and wrote
-// its results, and the first slab of a job waited for the results of the one before (gate/up + down, us, before /
-// now: B=512, d=2048, I=768 139 + 83 / 136 + 83; B=1000, d=4096, I=1536 560 + 330 / 549 + 319).
+// kernel without its results 6.3 to 6.5.  What is left are the results (kernel trace, with / without them: B=512, d=2048, I=768
+// gate/up 148 / 139 us, down 81 / 67; B=1000, d=4096, I=1536 555 / 520 and 315 / 255), in the down stage the adds into `out`
+// themselves: taking the multiplying wavefronts' own loads out, which had waited for them, gave 2 and 3 us.  In the form
+// in which every wavefront loaded into registers, multiplied and wrote, the first slab of a job waited for the results of
+// the one before (gate/up + down, us, that / this on one box: B=512, d=2048, I=768 139 + 83 / 136 + 83; B=1000, d=4096,
+// I=1536 560 + 330 / 549 + 319; other boxes have had 545 to 578 for that gate/up stage).
 #include "oea_ffn_dev.h"
 
 namespace oea {
@@ -155,7 +157,10 @@ struct DenseRing {
 // Waits until at most n of this wavefront's requests (a multiple of four) are outstanding.
 __device__ __forceinline__ void wait_outstanding(int n) {
   switch (n >> 2) {
-#define OEA_CASE(Q)                                               case Q:                                                           asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * Q) : "memory");     break;
+#define OEA_CASE(Q)                                              \
+  case Q:                                                        \
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * Q) : "memory"); \
+    break;
     OEA_CASE(1) OEA_CASE(2) OEA_CASE(3) OEA_CASE(4) OEA_CASE(5) OEA_CASE(6) OEA_CASE(7)
     OEA_CASE(8) OEA_CASE(9) OEA_CASE(10) OEA_CASE(11) OEA_CASE(12) OEA_CASE(13) OEA_CASE(14)
 #undef OEA_CASE
