@@ -307,6 +307,7 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   if (ex && ex->top_p > 0.0 && ex->top_p < 1.0) ga.p = ex->top_p;
   if (ex && ex->max_p > 0 && ex->max_p < N) ga.max_p = ex->max_p;
   const bool general = ga.p < 1.0 || ga.max_p < N;
+  ga.deterministic = y != nullptr;
 
   auto report = [&](int stage, int kernels) {
     if (opts && opts->h_kernels) opts->h_kernels[stage] = kernels;
@@ -332,7 +333,7 @@ static int decode_enqueue(const void* x, const void* W_router, const void* W_gat
   } else {
     e = launch_router_and_route(x, W_router, ex ? ex->router_bias : nullptr, ex ? ex->token_mask : nullptr, B, d,
                                 N, k, k0, dt, logits, y ? y : out, y ? (size_t)B * k * d : (size_t)B * d,
-                                reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, general ? &ga : nullptr, y != nullptr, s);
+                                reinterpret_cast<uint32_t*>(ws + w.ctrl), ro, &ga, s);
     if (e != hipSuccess || !mark(1) || !mark(2)) return OEA_ERR_HIP;
     const bool gate_up_stage = path == 3 || (path == 0 && prefer_stage_kernels(0, B, N, k, k0, I, d, elem_bytes_of(dt)));
     const bool down_stage = path == 3 || (path == 0 && prefer_stage_kernels(1, B, N, k, k0, d, I, elem_bytes_of(dt)));

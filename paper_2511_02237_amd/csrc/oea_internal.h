@@ -97,11 +97,13 @@ struct RouteOut {
   int32_t* grp_pos;  // may be nullptr: [B*k] position of each (token, slot) in the grouped order
 };
 
-// parameters of the general OEA routing (Algorithm 2) beyond k0: top-p threshold, cap, rank window
+// parameters of the general OEA routing (Algorithm 2) beyond k0: top-p threshold, cap, rank window; and whether the
+// layer's combine is deterministic (which kernels route is then a matter of B = 128, the line of its other kernels)
 struct RouteGeneralArgs {
   double p;
   int k_max;
   int max_p;
+  bool deterministic = false;
 };
 
 // launchers (each returns the hipError_t of the launch)
@@ -113,11 +115,10 @@ hipError_t launch_route(const float* logits, const uint8_t* token_mask, int L, i
 // the same with a lane per token, for launches of many positions; hipErrorNotSupported otherwise
 hipError_t try_launch_route_lanes(const float* logits, const uint8_t* token_mask, int L, int B, int N, int k, int k0,
                                   RouteOut o, hipStream_t s);
-// deterministic: which kernels route is a matter of B = 128, the line of the deterministic layers' other kernels
 hipError_t launch_router_and_route(const void* x, const void* w_router, const float* bias,
                                    const uint8_t* token_mask, int B, int d, int N, int k, int k0,
                                    oea_dtype dt, float* logits, float* to_zero, size_t n_zero, uint32_t* counter,
-                                   RouteOut o, const RouteGeneralArgs* general, bool deterministic, hipStream_t s);
+                                   RouteOut o, const RouteGeneralArgs* general, hipStream_t s);
 hipError_t launch_route_general(const float* logits, const uint8_t* token_mask, int B, int N, int k0,
                                 const RouteGeneralArgs& ga, int32_t* n_base, RouteOut o, hipStream_t s);
 // most experts a workgroup's rows may belong to

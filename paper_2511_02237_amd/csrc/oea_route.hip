@@ -530,11 +530,11 @@ hipError_t launch_route(const float* logits, const uint8_t* token_mask, int L, i
 template <typename WT>
 static hipError_t launch_rr(const void* x, const void* w_router, const float* bias, const uint8_t* token_mask,
                             int B, int d, int N, int k, int k0, float* logits, float* out_to_zero, size_t n_zero,
-                            uint32_t* counter, RouteOut o, const RouteGeneralArgs* ga, bool deterministic, hipStream_t s) {
+                            uint32_t* counter, RouteOut o, const RouteGeneralArgs* ga, hipStream_t s) {
   RouteGeneral g{1.0, k, N, nullptr};
   const int general = ga && (ga->p < 1.0 || ga->max_p < N) ? 1 : 0;
   if (general) g = RouteGeneral{ga->p, k, ga->max_p, nullptr};
-  if (B > (deterministic ? kWideFromBatchDeterministic : kWideFromBatch) && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
+  if (B > (ga && ga->deterministic ? kWideFromBatchDeterministic : kWideFromBatch) && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
     // large batch: router and routing over many workgroups, four kernels in stream order
     const int per_wg = kWideThreads / 64;  // a wavefront per token; small workgroups spread them over the compute units
     hipLaunchKernelGGL((wide_logits_kernel<WT>), dim3((B + 15) / 16, (N + 15) / 16), dim3(64 * kLogitWaves), 0, s,
@@ -590,12 +590,10 @@ static hipError_t launch_rr(const void* x, const void* w_router, const float* bi
 hipError_t launch_router_and_route(const void* x, const void* w_router, const float* bias,
                                    const uint8_t* token_mask, int B, int d, int N, int k, int k0,
                                    oea_dtype dt, float* logits, float* to_zero, size_t n_zero, uint32_t* counter,
-                                   RouteOut o, const RouteGeneralArgs* ga, bool deterministic, hipStream_t s) {
+                                   RouteOut o, const RouteGeneralArgs* ga, hipStream_t s) {
   if (dt == OEA_F32)
-    return launch_rr<float>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga,
-                            deterministic, s);
-  return launch_rr<uint16_t>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga,
-                             deterministic, s);
+    return launch_rr<float>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga, s);
+  return launch_rr<uint16_t>(x, w_router, bias, token_mask, B, d, N, k, k0, logits, to_zero, n_zero, counter, o, ga, s);
 }
 
 hipError_t launch_route_general(const float* logits, const uint8_t* token_mask, int B, int N, int k0,
