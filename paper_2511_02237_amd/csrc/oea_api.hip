@@ -54,16 +54,17 @@ static int check_route_sizes(int B, int N, int k, int k0) {
 //   single kernel, d=2048, I=768, N=128, k=8   k0=3: 5.1 pairs 177 / 187 (B=64), 5.9 198 / 197, 6.7 213 / 211,
 //                                               7.5 234 / 215, 8.4 240 / 227 (B=128); k0=1: 11.4 167 / 144; k0=8: 6.0 232 / 237
 //   single kernel, d=4096, I=1536, N=128, k=8  k0=3: 3.9 435 / 440 (B=32), 4.4 556 / 552, 5.1 646 / 631, 5.9 712 / 683,
-//                                               8.4 1102 / 789 (B=128); k0=1: 10 440 / 345; k0=8: 4.1 784 / 783, 5.0 787 / 828
-//                                               and 784 / 834 (B=80), 6.0 928 / 778 and 840 / 783; again on other boxes: k0=3: 5.1
-//                                               646 / 627 and 611 / 609, 5.9 708 / 683 and 719 / 665; k0=2: 5.5 436 / 443 and 437 / 447
+//                                               8.4 1102 / 789 (B=128); k0=1: 10 440 / 345; k0=8: 4.1 784 / 783;
+//                                               with other weights and tokens, twice: k0=2 5.7 436 / 443, 437 / 447 (B=48); k0=3
+//                                               5.1 646 / 627, 611 / 609, 5.9 708 / 683, 719 / 665 (B=80); k0=8 5.0 787 / 828,
+//                                               784 / 834 (B=80), 6.0 928 / 778, 840 / 783
 //   dot-product kernels (the better of streaming and stage kernels)
 //                  d=4096, I=192, N=128, k0=3  3.0 56 / 60 (B=16), 3.4 72 / 70, 4.4 107 / 101, 5.1 125 / 109, 8.5 187 / 133 (B=130)
 //                  d=512, I=512, N=60, k0=3    3.2 31 / 27 (B=9), 5.6 46 / 33;  d=512, I=192, N=64  3.1 29 / 26 (B=32), 8.3 48 / 34
 //                  d=1024, I=256, N=24         4.9 29 / 27 (B=9), 12 40 / 30;   d=64, I=64, N=16    3.2 23 / 22 (B=9), 17 40 / 24
 //                  d=2048, I=1024, N=160, k0=1 1.8 85 / 82 (B=32), 2.4 145 / 148, 2.9 213 / 210
-//   max_p, k0=3    d=4096, I=1536 3 of 128 1.9 582 / 622 (B=64), 8 4.4 623 / 646;  d=4096, I=192 3 of 128 1.4 79 / 82 (B=32), 2.6 125 /
-//                  126 (B=100), 8 6.5 154 / 127
+//   rank window, k0=3  d=4096, I=1536 max_p=3 1.9 582 / 622 (B=64), max_p=8 4.4 623 / 646;  d=4096, I=192 max_p=3 1.4 79 / 82
+//                  (B=32), 2.6 125 / 126 (B=100), max_p=8 6.5 154 / 127
 static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, int max_p) {
   const double active = N * (1.0 - std::pow(1.0 - double(k0) / N, B));
   const double selects = max_p > k0 ? k0 + (max_p - k0) * (active - k0) / (N - k0) : k0;
@@ -73,23 +74,23 @@ static bool pairs_for_matrix_cores(int B, int d, int N, int I, int k, int k0, in
     // need for the weights (5.5 TB/s) and the pairs (d=4096, I=192, k0=2: B=8 42 / 48, B=12 48 / 55; d=1024, I=256,
     // k0=1: B=4 24 / 27, B=12 31 / 28; d=2048, I=1024, k0=1: B=6 43 / 45, B=8 50 / 45)
     const double walk = 0.45 * (d + I) / 64, other = active * 6.0 * d * I / 5.5e6 + 1.2 * pairs;
-    // (the single kernel's layers with more experts or more experts per token than it takes: d=2048, I=768, N=160 4.6 217 / 226
-    // and 221 / 211 (B=64), 5.2 239 / 244, 6.7 284 / 259; d=4096, I=1536, N=160 4.7 729 / 699; k=20 5.0 53 / 47, 9.6 158 / 140 and
-    // 573 / 438)
-    // Experts of 12 MB and more stream for so long that the pairs are hidden for longer, on rows of up to 4096 (k0=3, d=4096, I=1024,
-    // N=128 3.3 212 / 212 and 209 / 220 (B=20), 3.9 289 / 298 and 300 / 312, 4.5 372 / 366 and 346 / 348, 5.1 448 / 421; d=2048,
-    // I=1024 3.9 163 / 167, 4.4 200 / 191 and 200 / 203, 5.1 233 / 225; d=2048, I=1408, N=64, k=6 3.4 139 / 146 and 140 / 138, 4.7
-    // 174 / 176 and 176 / 166; longer rows, d=5120, I=1536, N=160, k=6 3.7 1161 / 818).
+    // The single kernel's layers with more experts, or more experts per token, than it takes: d=2048, I=768, N=160 4.6
+    // 217 / 226, 221 / 211 (B=64), 5.2 239 / 244, 6.7 284 / 259; d=4096, I=1536, N=160 4.7 729 / 699; k=20, N=128, d=2048
+    // 5.0 53 / 47, 9.6 158 / 140, d=4096 9.6 573 / 438.
+    // Experts of 12 MB and more stream for so long that the pairs are hidden for longer, on rows of up to 4096 (k0=3,
+    // d=4096, I=1024, N=128 3.3 212 / 212, 209 / 220 (B=20), 3.9 289 / 298, 300 / 312, 4.5 372 / 366, 346 / 348, 5.1
+    // 448 / 421; d=2048, I=1024 3.9 163 / 167, 4.4 200 / 191, 200 / 203, 5.1 233 / 225; d=2048, I=1408, N=64, k=6 3.4
+    // 139 / 146, 140 / 138, 4.7 174 / 176, 176 / 166; longer rows, d=5120, I=1536, N=160, k=6 3.7 1161 / 818).
     const double line = fused_kernel_shape(d, I) ? 5.5 : d <= 4096 && d * I >= (2 << 20) ? 4.4 : 3.2;
     return B > 4 && pairs >= line && walk <= other;
   }
   // on a batch that stays the same the single kernel's speed weights settle, and at d=2048 it leads up to B=128, k0=3
-  return d == 4096 ? B >= 48 && pairs >= 5.9 : B > 64 && pairs >= 9.0;
+  return d == 4096 ? B >= 48 && pairs >= 5.8 : B > 64 && pairs >= 9.0;
 }
 
 // Whether the expert stages run on the matrix cores where their kernels fit: always above the single kernel's range of
-// batches with d a multiple of 256 and I of 128 (B=130, k=k0=1, 1.1 pairs, d=2048, I=384, N=512 141 / 122; d=4096, N=128 I=384,
-// 1.6 pairs 153 / 159, I=640 238 / 243), else where an active expert serves enough pairs.
+// batches with d a multiple of 256 and I of 128 (B=130, k=k0=1, d=2048, I=384, N=512 1.1 pairs 141 / 122; d=4096, N=128,
+// I=384 1.6 pairs 153 / 159, I=640 238 / 243), else where an active expert serves enough pairs.
 // With the deterministic combine the line is B = 128 alone: below it the kernels give a token the same bits in
 // every batch (above a handful of tokens, where small stages change kernels), above it the matrix cores do.
 static bool prefer_matrix_cores(int B, int d, int N, int I, int k, int k0, const RouteGeneralArgs& ga, bool masked,

@@ -25,8 +25,8 @@
 // gate/up 148 / 139 us, down 81 / 67; B=1000, d=4096, I=1536 555 / 520 and 315 / 255), in the down stage the adds into `out`
 // themselves: taking the multiplying wavefronts' own loads out, which had waited for them, gave 2 and 3 us.  In the form
 // in which every wavefront loaded into registers, multiplied and wrote, the first slab of a job waited for the results of
-// the one before (gate/up + down, us, that / this on one box: B=512, d=2048, I=768 139 + 83 / 136 + 83; B=1000, d=4096,
-// I=1536 560 + 330 / 549 + 319; other boxes have had 545 to 578 for that gate/up stage).
+// the one before (gate/up + down, us, that / this, in turn on one card: B=512, d=2048, I=768 139 + 83 / 136 + 83;
+// B=1000, d=4096, I=1536 560 + 330 / 549 + 319; other cards and allocations have had 545 to 578 for that gate/up stage).
 #include "oea_ffn_dev.h"
 
 namespace oea {

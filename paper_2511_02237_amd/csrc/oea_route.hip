@@ -163,8 +163,8 @@ __global__ __launch_bounds__(kRouteThreads) void router_route_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batches above 96 tokens (128 with the deterministic combine): router and routing over many workgroups, as four kernels in stream
-// order (a kernel boundary is the grid-wide synchronisation Algorithm 1 needs twice: the union of
+// Batches above 96 tokens (128 with the deterministic combine): router and routing over many workgroups, as four kernels
+// in stream order (a kernel boundary is the grid-wide synchronisation Algorithm 1 needs twice: the union of
 // Phase 1 before Phase 2, all pair counts before the grouped lists).  The union and the counts live
 // in control words of the workspace that the first kernel clears.  With one workgroup per expert
 // for the logits and one workgroup routing the whole batch this step took 50 / 104 / 230 us at
@@ -534,7 +534,8 @@ static hipError_t launch_rr(const void* x, const void* w_router, const float* bi
   RouteGeneral g{1.0, k, N, nullptr};
   const int general = ga && (ga->p < 1.0 || ga->max_p < N) ? 1 : 0;
   if (general) g = RouteGeneral{ga->p, k, ga->max_p, nullptr};
-  if (B > (ga && ga->deterministic ? kWideFromBatchDeterministic : kWideFromBatch) && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
+  const int wide_from = ga && ga->deterministic ? kWideFromBatchDeterministic : kWideFromBatch;
+  if (B > wide_from && o.grp_off && o.grp_tok && o.grp_gw && o.grp_pos) {
     // large batch: router and routing over many workgroups, four kernels in stream order
     const int per_wg = kWideThreads / 64;  // a wavefront per token; small workgroups spread them over the compute units
     hipLaunchKernelGGL((wide_logits_kernel<WT>), dim3((B + 15) / 16, (N + 15) / 16), dim3(64 * kLogitWaves), 0, s,

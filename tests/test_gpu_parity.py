@@ -275,7 +275,7 @@ D30, D235 = (2048, 128, 768, 8), (4096, 128, 1536, 8)
     ((2048, 160, 768, 8), 64, 3, {}, "dot"), ((2048, 160, 768, 8), 128, 3, {}, "matrix"), ((2048, 128, 768, 20), 32, 3, {}, "matrix"),
     ((4096, 128, 1536, 20), 32, 3, {}, "matrix"), ((4096, 128, 1536, 16), 64, 8, {}, "matrix"),
     # experts of all tokens' own choice, few pairs on each; large experts
-    (D235, 80, 8, {}, "single"), (D235, 96, 8, {}, "matrix"), (D235, 48, 2, {}, "single"), (D235, 48, 1, {}, "matrix"),
+    (D235, 80, 8, {}, "single"), (D235, 80, 3, {}, "matrix"), (D235, 72, 3, {}, "single"), (D235, 96, 8, {}, "matrix"), (D235, 48, 2, {}, "single"), (D235, 48, 1, {}, "matrix"),
     ((4096, 128, 1024, 8), 32, 3, {}, "dot"), ((4096, 128, 1024, 8), 64, 3, {}, "matrix"), ((5120, 64, 512, 8), 24, 3, {}, "matrix"),
     # with the deterministic combine above B = 128 alone
     (D235, 128, 3, dict(deterministic=True), "single"), (D235, 129, 3, dict(deterministic=True), "matrix"),
